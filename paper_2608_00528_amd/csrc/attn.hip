@@ -204,140 +204,240 @@ static void launch_combine_t(const Problem& P, const Workspace& ws, int64_t L, i
 // ---------------------------------------------------------------------------
 // explicit reconstruction: K^[b, n, :] = C^K[b, idx[b, n]] (B^K)^T (fp32 out)
 // ---------------------------------------------------------------------------
-// grid (ceil(m / 16), h_kv, B), one wave: 16 tokens x d_h dims of head j.
+// grid (ceil(m / 16), h_kv, B), four waves: wave w forms the key (w < 2) or
+// value rows of 16 tokens over half w % 2 of head j's dims.  Bound by latency
+// at decode sizes (m = 1088, 8 heads: 9 MB written), so every basis block of a
+// dims step is requested before the first product, and the basis is the A
+// operand: a lane then holds four consecutive dims of one token and stores 16
+// bytes.  15.3 -> 11.8 us at m = 1088, rank 160 (one wave per 16 tokens walking
+// both sides and all dims before).
 template <typename T, int RBH>
-__global__ __launch_bounds__(64) void k_reconstruct(
+__global__ __launch_bounds__(256) void k_reconstruct(
     const int32_t* __restrict__ idx_all, const T* __restrict__ bases_k, const T* __restrict__ bases_v,
     const T* __restrict__ coef_k, const T* __restrict__ coef_v, float* __restrict__ k_hat,
     float* __restrict__ v_hat, int m, int hkv, int dh, int nb, int rank, int R, int64_t L, int64_t cap,
     int bases_shared) {
   constexpr int NP = Parts<T>::n;
   const int tile = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x, slot = lane & 15, kg = lane >> 4;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, slot = lane & 15, kg = lane >> 4;
+  const int which = w >> 1, half = w & 1;
   const int Dp = hkv * dh, Dg = Dp / nb;
   const int grp = j / (hkv / nb), row0 = (j % (hkv / nb)) * dh, kb0 = grp * rank / 32;
   const int n = tile * 16 + slot;
   int64_t tok = (n < m) ? (int64_t)idx_all[(int64_t)b * m + n] : 0;
-  const bool bad = (n < m) && (tok < 0 || tok >= L);
+  const bool bad = tok < 0 || tok >= L;            // NaN row instead of a read out of range
   if (bad) tok = 0;
   const int64_t co = (tok >> 4) * 16 * (int64_t)R + (tok & 15) * 32 + kg * 8;
   const int64_t boff = (bases_shared ? 0 : (int64_t)b * Dp * rank) + (int64_t)grp * Dg * rank;
-  for (int which = 0; which < 2; ++which) {
-    const T* cb = (which == 0 ? coef_k : coef_v) + (int64_t)b * cap * R;
-    const T* bb = (which == 0 ? bases_k : bases_v) + boff;
-    float* dst = which == 0 ? k_hat : v_hat;
-    Op8 a[RBH][NP];
+  const T* cb = (which == 0 ? coef_k : coef_v) + (int64_t)b * cap * R;
+  const T* bb = (which == 0 ? bases_k : bases_v) + boff;
+  float* dst = (which == 0 ? k_hat : v_hat) + ((int64_t)b * m + n) * Dp + (int64_t)j * dh;
+  Op8 c[RBH][NP];
 #pragma unroll
-    for (int kb = 0; kb < RBH; ++kb) Parts<T>::load(cb + co + (int64_t)(kb0 + kb) * 512, a[kb]);
-    for (int nbk = 0; nbk < dh / 16; ++nbk) {
+  for (int kb = 0; kb < RBH; ++kb) Parts<T>::load(cb + co + (int64_t)(kb0 + kb) * 512, c[kb]);
+  const int nblk = dh / 32;                        // 16-dim blocks of this wave's half
+  constexpr int BST = NP == 1 ? 2 : 1;             // blocks per step (nblk is 2 or 4)
+  for (int i0 = 0; i0 < nblk; i0 += BST) {
+    Op8 bo[BST][RBH][NP];
+#pragma unroll
+    for (int u = 0; u < BST; ++u)
+#pragma unroll
+      for (int kb = 0; kb < RBH; ++kb)
+        Parts<T>::load(bb + (int64_t)(row0 + (half * nblk + i0 + u) * 16 + slot) * rank + kb * 32 + kg * 8, bo[u][kb]);
+    if constexpr (NP == 1) __builtin_amdgcn_sched_barrier(0);   // the loads stay together, ahead of the products
+#pragma unroll
+    for (int u = 0; u < BST; ++u) {
       floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kb = 0; kb < RBH; ++kb) {
-        Op8 bo[NP];
-        Parts<T>::load(bb + (int64_t)(row0 + nbk * 16 + slot) * rank + kb * 32 + kg * 8, bo);
-        d = mfma_parts<NP, NP>(a[kb], bo, d);
-      }
-      // lane holds rows (tokens) 4*kg + v of the tile, column (dim) slot
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int nn = tile * 16 + kg * 4 + v;
-        if (nn < m) dst[((int64_t)b * m + nn) * Dp + (int64_t)j * dh + nbk * 16 + slot] = d[v];
-      }
-    }
-  }
-  // rows with an out-of-range index are set to NaN instead of being read
-  if (bad) {
-    for (int d = 0; d < dh; ++d) {
-      k_hat[((int64_t)b * m + n) * Dp + (int64_t)j * dh + d] = __int_as_float(0x7fc00000);
-      v_hat[((int64_t)b * m + n) * Dp + (int64_t)j * dh + d] = __int_as_float(0x7fc00000);
+      for (int kb = 0; kb < RBH; ++kb) d = mfma_parts<NP, NP>(bo[u][kb], c[kb], d);
+      if (bad) d = floatx4{NAN, NAN, NAN, NAN};
+      // lane holds token slot, dims 4 kg + v of the block
+      if (n < m) *reinterpret_cast<floatx4*>(dst + (half * nblk + i0 + u) * 16 + kg * 4) = d;
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// explicit attention over given fp32 rows (plus sinks)
+// explicit attention over given fp32 rows
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_sparse_attn(
-    const T* __restrict__ q, const T* __restrict__ sink_k, const T* __restrict__ sink_v,
-    const int32_t* __restrict__ idx_all, const float* __restrict__ k_sel, const float* __restrict__ v_sel,
-    float* __restrict__ out, float* __restrict__ logits_all, int m, int hq, int hkv, int dh, int s_sink,
-    int64_t L, int64_t logit_stride, float theta) {
-  const int h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-  const int G = hq / hkv, j = h / G, Dp = hkv * dh;
-  const int n_all = s_sink + m;
-  float* lg = logits_all + ((int64_t)b * hq + h) * logit_stride;
-  __shared__ float qr[128];
-  __shared__ double rfs[64];
-  __shared__ float red[1024];
-  __shared__ float s_mx, s_sum;
-  if (t < dh / 2) rfs[t] = rope_rev_freq(theta, t, dh);
-  if (t < dh / 2) {
-    float c, sn;
-    rope_cs(s_sink + L - 1, rfs[t], c, sn);
-    const int64_t qo = ((int64_t)b * hq + h) * dh;
-    const float xl = load_elem(q, qo + t), xh = load_elem(q, qo + t + dh / 2);
-    qr[t] = xl * c - xh * sn;
-    qr[t + dh / 2] = xh * c + xl * sn;
-  }
-  __syncthreads();
-  for (int e = t; e < n_all; e += blockDim.x) {
-    float acc = 0.f;
-    int64_t pos;
-    if (e < s_sink) {
-      pos = e;
-      const T* kp = sink_k + ((int64_t)b * s_sink + e) * Dp + (int64_t)j * dh;
-      for (int f = 0; f < dh / 2; ++f) {
-        float c, sn;
-        rope_cs(pos, rfs[f], c, sn);
-        const float xl = load_elem(kp, f), xh = load_elem(kp, f + dh / 2);
-        acc = fmaf(qr[f], xl * c - xh * sn, acc);
-        acc = fmaf(qr[f + dh / 2], xh * c + xl * sn, acc);
+// grid (row splits, h_kv, B), four waves: a workgroup attends one KV head's G
+// query heads to its share of the rows, in chunks of 32 with one running
+// maximum per head, and leaves a split partial that k_attn_combine merges with
+// the sinks.  A row's RoPE pair f sits in lane f (d_h = 128; two rows per wave
+// at d_h = 64), so a wave reads whole rows, and the 8 rows x up to 4 heads of
+// dot products are summed over the lanes by halving exchanges (31 instead of
+// 192).  Both the key and the value rows of a chunk are requested before any
+// is used.  Reading the rows bounds it (8 bytes per row element) once the
+// splits fill the chip; the single workgroup per query head that it replaces,
+// whose threads walked all rows of V one by one, took 334 us at m = 1088, 8 KV
+// heads, against 7.3 us.
+constexpr int kSaRows = 32;            // rows per chunk
+
+// sums of N values over the 2 O lanes that differ in the bits O, O / 2, .., 1:
+// while several values are left a lane keeps half of them and adds its
+// partner's sums of those, then plain exchanges; the lane whose bits under 2 O
+// are f ends with value f / (2 O / N) in v[0] (N <= 2 O).  Recursive, so every
+// index is a constant: a loop over a shrinking count became 7000 instructions
+// of selects, past what the instruction cache holds.
+template <int N, int O>
+__device__ __forceinline__ void lane_sums(float* v, int lane) {
+  if constexpr (O > 0) {
+    if constexpr (N > 1) {
+      const bool up = (lane & O) != 0;
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) {
+        const float keep = up ? v[i + N / 2] : v[i], send = up ? v[i] : v[i + N / 2];
+        v[i] = keep + shfl_xor_f(send, O);
       }
+      lane_sums<N / 2, O / 2>(v, lane);
     } else {
-      const int n = e - s_sink;
-      pos = s_sink + (int64_t)idx_all[(int64_t)b * m + n];
-      const float* kp = k_sel + ((int64_t)b * m + n) * Dp + (int64_t)j * dh;
-      for (int f = 0; f < dh / 2; ++f) {
-        float c, sn;
-        rope_cs(pos, rfs[f], c, sn);
-        const float xl = kp[f], xh = kp[f + dh / 2];
-        acc = fmaf(qr[f], xl * c - xh * sn, acc);
-        acc = fmaf(qr[f + dh / 2], xh * c + xl * sn, acc);
+      v[0] += shfl_xor_f(v[0], O);
+      lane_sums<1, O / 2>(v, lane);
+    }
+  }
+}
+template <typename T, int DH, int GB>
+__global__ __launch_bounds__(256) void k_sparse_attn(
+    const T* __restrict__ q, const int32_t* __restrict__ idx_all, const float* __restrict__ k_sel,
+    const float* __restrict__ v_sel, float* __restrict__ part_ml, float* __restrict__ part_o, int m,
+    int rows_per_split, int G, int hq, int hkv, int s_sink, int64_t L, double rope_ratio) {
+  constexpr int HALF = DH / 2;                     // lanes per row
+  constexpr int RPW = kSaRows / 4;                 // rows per wave (8)
+  constexpr int PAR = 64 / HALF;                   // rows side by side in a wave
+  constexpr int RPL = RPW / PAR;                   // rows per lane
+  constexpr int GP = GB < 4 ? GB : 4;              // heads per reduction
+  constexpr int NV = RPL * GP;                     // values per reduction (<= lanes per row)
+  constexpr int NPH = 256 / DH;                    // row phases of the value pass
+  const int split = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int f = lane % HALF, par = lane / HALF;
+  const int Dp = hkv * DH;
+  const int r_begin = split * rows_per_split, r_end = min(m, r_begin + rows_per_split);   // r_begin < m
+  __shared__ float sl[GB][kSaRows];
+  __shared__ float s_alpha[GB];
+  __shared__ float red[NPH][GB][DH];
+  const float* kb = k_sel + (int64_t)b * m * Dp + (int64_t)j * DH;
+  const float* vb = v_sel + (int64_t)b * m * Dp + (int64_t)j * DH;
+  const int32_t* idx = idx_all + (int64_t)b * m;
+  uint64_t F[4];
+  rope_freqs_fixed(rope_ratio, f, F);
+  float ql[GB], qh[GB];
+  {
+    float c, sn;
+    rope_cs_fixed(s_sink + L - 1, F[0], c, sn);
+    const float inv = 1.0f / sqrtf((float)DH);
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+      const int64_t qo = ((int64_t)b * hq + (int64_t)j * G + min(g, G - 1)) * DH;
+      const float xl = load_elem(q, qo + f), xh = load_elem(q, qo + f + HALF);
+      ql[g] = (xl * c - xh * sn) * inv;
+      qh[g] = (xh * c + xl * sn) * inv;
+    }
+  }
+  const int dim = t % DH, ph = t / DH;
+  float acc[GB];
+#pragma unroll
+  for (int g = 0; g < GB; ++g) acc[g] = 0.f;
+  // softmax state of heads w, w + 4, .. (every lane of wave w holds the same)
+  constexpr int GW = (GB + 3) / 4;
+  float Mr[GW], lr[GW];
+#pragma unroll
+  for (int i = 0; i < GW; ++i) {
+    Mr[i] = -INFINITY;
+    lr[i] = 0.f;
+  }
+  for (int r0 = r_begin; r0 < r_end; r0 += kSaRows) {
+    float kl[RPL], kh[RPL], vv[kSaRows / NPH];
+    int32_t pos[RPL];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      const int r = min(r0 + w * RPW + par * RPL + i, r_end - 1);
+      kl[i] = kb[(int64_t)r * Dp + f];
+      kh[i] = kb[(int64_t)r * Dp + f + HALF];
+      pos[i] = idx[r];
+    }
+#pragma unroll
+    for (int i = 0; i < kSaRows / NPH; ++i) vv[i] = vb[(int64_t)min(r0 + i * NPH + ph, r_end - 1) * Dp + dim];
+    __builtin_amdgcn_sched_barrier(0);             // every load of the chunk is requested before any is used
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      float c, sn;
+      rope_cs_fixed((int64_t)s_sink + pos[i], F[0], c, sn);
+      const float a = kl[i] * c - kh[i] * sn, d = kh[i] * c + kl[i] * sn;
+      kl[i] = a;
+      kh[i] = d;
+    }
+    for (int g0 = 0; g0 < GB; g0 += GP) {
+      float v[NV];
+#pragma unroll
+      for (int g = 0; g < GP; ++g)
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+          // g0 + g by compile-time selection (the query stays in registers)
+          float a = 0.f, d = 0.f;
+#pragma unroll
+          for (int gg = g; gg < GB; gg += GP) {
+            a = (gg == g0 + g) ? ql[gg] : a;
+            d = (gg == g0 + g) ? qh[gg] : d;
+          }
+          v[g * RPL + i] = fmaf(a, kl[i], d * kh[i]);
+        }
+      lane_sums<NV, HALF / 2>(v, lane);
+      constexpr int REP = HALF / NV;               // lanes that end with the same value
+      const int vi = f / REP, row = w * RPW + par * RPL + vi % RPL;
+      if (f % REP == 0) sl[g0 + vi / RPL][row] = (r0 + row < r_end) ? v[0] : -INFINITY;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < GW; ++i) {
+      const int g = w + 4 * i;
+      if (g < GB) {
+        const float x = sl[g][lane & 31];
+        float mx = slot_max16(x);
+        mx = fmaxf(mx, shfl_xor_f(mx, 16));
+        const float mn = fmaxf(Mr[i], mx);         // finite logits: row r0 is always live; NaN rows give NaN
+        const float al = (Mr[i] == -INFINITY) ? 0.f : __expf(Mr[i] - mn);
+        const float p = (x == -INFINITY) ? 0.f : __expf(x - mn);
+        float sm = slot_sum16(p);
+        sm += shfl_xor_f(sm, 16);
+        lr[i] = lr[i] * al + sm;
+        Mr[i] = mn;
+        if (lane < 32) sl[g][lane] = p;
+        if (lane == 0) s_alpha[g] = al;
       }
     }
-    lg[e] = acc / sqrtf((float)dh);
-  }
-  __syncthreads();
-  float mx = -INFINITY;
-  for (int e = t; e < n_all; e += blockDim.x) mx = fmaxf(mx, lg[e]);
-  red[t] = mx;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] = fmaxf(red[t], red[t + o]);
-    __syncthreads();
-  }
-  if (t == 0) s_mx = red[0];
-  __syncthreads();
-  float sm = 0.f;
-  for (int e = t; e < n_all; e += blockDim.x) sm += __expf(lg[e] - s_mx);
-  red[t] = sm;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] += red[t + o];
-    __syncthreads();
-  }
-  if (t == 0) s_sum = red[0];
-  __syncthreads();
-  if (t < dh) {
-    float o = 0.f;
-    for (int e = 0; e < n_all; ++e) {
-      const float p = __expf(lg[e] - s_mx);
-      const float v = (e < s_sink) ? load_elem(sink_v, ((int64_t)b * s_sink + e) * Dp + (int64_t)j * dh + t)
-                                   : v_sel[((int64_t)b * m + (e - s_sink)) * Dp + (int64_t)j * dh + t];
-      o = fmaf(p, v, o);
+    lds_barrier();
+    // rows past the end weigh nothing (their slots repeat the last row, whose
+    // values may be infinite)
+#pragma unroll
+    for (int i = 0; i < kSaRows / NPH; ++i) vv[i] = (r0 + i * NPH + ph < r_end) ? vv[i] : 0.f;
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+      float a = acc[g] * s_alpha[g];
+#pragma unroll
+      for (int i = 0; i < kSaRows / NPH; ++i) a = fmaf(sl[g][i * NPH + ph], vv[i], a);
+      acc[g] = a;
     }
-    out[((int64_t)b * hq + h) * dh + t] = o / s_sum;
+    lds_barrier();                                 // sl is rewritten by the next chunk
+  }
+#pragma unroll
+  for (int g = 0; g < GB; ++g) red[ph][g][dim] = acc[g];
+  __syncthreads();
+  for (int i = t; i < G * DH; i += 256) {
+    const int g = i / DH, d = i % DH;
+    float o = 0.f;
+#pragma unroll
+    for (int k = 0; k < NPH; ++k) o += red[k][g][d];
+    part_o[(((int64_t)b * hq + (int64_t)j * G + g) * kMaxSplit + split) * DH + d] = o;
+  }
+#pragma unroll
+  for (int i = 0; i < GW; ++i) {
+    const int g = w + 4 * i;
+    if (g < G && lane == 0) {
+      float* ml = part_ml + (((int64_t)b * hq + (int64_t)j * G + g) * kMaxSplit + split) * 2;
+      ml[0] = Mr[i];
+      ml[1] = lr[i];
+    }
   }
 }
 
@@ -449,7 +549,7 @@ hipError_t launch_combine_only(const Problem& P, const Workspace& ws, int64_t L,
 template <typename T, int RBH>
 static void launch_rec_t(const Problem& P, int64_t L, int m, const int32_t* idx, const void* bk, const void* bv,
                          const void* ck, const void* cv, float* kh, float* vh, hipStream_t st) {
-  hipLaunchKernelGGL((k_reconstruct<T, RBH>), dim3((m + 15) / 16, P.hkv, P.B), dim3(64), 0, st, idx, (const T*)bk,
+  hipLaunchKernelGGL((k_reconstruct<T, RBH>), dim3((m + 15) / 16, P.hkv, P.B), dim3(256), 0, st, idx, (const T*)bk,
                      (const T*)bv, (const T*)ck, (const T*)cv, kh, vh, m, P.hkv, P.dh, P.nb, P.rank, P.R, L, P.cap,
                      P.bases_shared);
 }
@@ -481,18 +581,39 @@ hipError_t launch_reconstruct(const Problem& P, int64_t L, int m, const int32_t*
   return hipGetLastError();
 }
 
+// row splits of the explicit attention: about two workgroups per CU over the
+// batch (one chunk of rows each, or fewer rows, while that leaves the chip
+// idle), at most kMaxSplit
+template <typename T, int DH>
+static int launch_sparse_rows(const Problem& P, const Workspace& ws, int64_t L, int m, const void* q,
+                              const int32_t* idx, const float* k_sel, const float* v_sel, hipStream_t st) {
+  int ns = std::max(1, std::min(kMaxSplit, 512 / std::max(1, P.B * P.hkv)));
+  const int rows = std::max(8, (m + ns - 1) / ns);
+  ns = (m + rows - 1) / rows;
+  auto kern = P.G <= 1   ? k_sparse_attn<T, DH, 1>
+              : P.G <= 2 ? k_sparse_attn<T, DH, 2>
+              : P.G <= 4 ? k_sparse_attn<T, DH, 4>
+              : P.G <= 8 ? k_sparse_attn<T, DH, 8> : k_sparse_attn<T, DH, 16>;
+  hipLaunchKernelGGL(kern, dim3(ns, P.hkv, P.B), dim3(256), 0, st, (const T*)q, idx, k_sel, v_sel, ws.part_ml,
+                     ws.part_o, m, rows, P.G, P.hq, P.hkv, P.s, L, rope_ratio(P));
+  return ns;
+}
+
 hipError_t launch_sparse_attn(const Problem& P, const Workspace& ws, int64_t L, int m, const void* q,
                               const void* sink_k, const void* sink_v, const int32_t* idx, const float* k_sel,
                               const float* v_sel, float* out, hipStream_t st) {
-  const int64_t stride = P.s + P.m_max;
-  if (P.dtype == S4R_BF16)
-    hipLaunchKernelGGL(k_sparse_attn<uint16_t>, dim3(P.hq, P.B), dim3(256), 0, st, (const uint16_t*)q,
-                       (const uint16_t*)sink_k, (const uint16_t*)sink_v, idx, k_sel, v_sel, out, ws.attn_logits, m,
-                       P.hq, P.hkv, P.dh, P.s, L, stride, P.theta);
-  else
-    hipLaunchKernelGGL(k_sparse_attn<float>, dim3(P.hq, P.B), dim3(256), 0, st, (const float*)q,
-                       (const float*)sink_k, (const float*)sink_v, idx, k_sel, v_sel, out, ws.attn_logits, m, P.hq,
-                       P.hkv, P.dh, P.s, L, stride, P.theta);
+  int ns = 0;
+  if (P.dtype == S4R_BF16) {
+    if (m > 0)
+      ns = P.dh == 128 ? launch_sparse_rows<uint16_t, 128>(P, ws, L, m, q, idx, k_sel, v_sel, st)
+                       : launch_sparse_rows<uint16_t, 64>(P, ws, L, m, q, idx, k_sel, v_sel, st);
+    launch_combine_t<uint16_t>(P, ws, L, ns, q, sink_k, sink_v, nullptr, nullptr, P.s, 0, out, st);
+  } else {
+    if (m > 0)
+      ns = P.dh == 128 ? launch_sparse_rows<float, 128>(P, ws, L, m, q, idx, k_sel, v_sel, st)
+                       : launch_sparse_rows<float, 64>(P, ws, L, m, q, idx, k_sel, v_sel, st);
+    launch_combine_t<float>(P, ws, L, ns, q, sink_k, sink_v, nullptr, nullptr, P.s, 0, out, st);
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,73 @@
+"""The separately callable reconstruction and attention over given rows, at the
+edges of their row splits, chunks of 32 rows, tiles of 16 and head groups."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_00528_amd as s4r
+from oracle import decode
+from tests.gpu_util import dev, rel_err_rows
+
+pytestmark = pytest.mark.gpu
+
+
+def _draw(hq, hkv, dh, rank, nb, n_sink, m, L, B, dtype, seed):
+    rng = np.random.default_rng(seed)
+    c = s4r.make_config(batch=B, n_q_heads=hq, n_kv_heads=hkv, head_dim=dh, rank=rank, basis_groups=nb,
+                        capacity=(L + 15) // 16 * 16, n_sink=n_sink, window=8, topk=max(m, 8) - 8,
+                        rope_theta=10000.0, dtype=dtype)
+    Dp, dt = hkv * dh, s4r.storage_dtype(c)
+    idx = np.stack([np.sort(rng.permutation(L)[:m]) for _ in range(B)]).reshape(B, m)
+    rnd = lambda *s: torch.from_numpy(rng.standard_normal(s)).to(dt)  # noqa: E731
+    return c, idx, rnd(B, hq, dh), rnd(B, n_sink, Dp), rnd(B, n_sink, Dp), rng
+
+
+@pytest.mark.parametrize("hq,hkv,dh,n_sink,m,B,dtype", [
+    (8, 2, 64, 4, 1, 1, "fp32"), (4, 4, 128, 0, 8, 2, "bf16"), (16, 8, 128, 4, 33, 1, "bf16"),
+    (28, 4, 128, 4, 64, 1, "bf16"), (32, 8, 128, 4, 513, 1, "fp32"), (32, 4, 64, 2, 1000, 3, "bf16"),
+    (16, 1, 128, 0, 2500, 1, "bf16"), (32, 8, 128, 4, 0, 1, "bf16"),
+])
+def test_attention_over_rows(hq, hkv, dh, n_sink, m, B, dtype):
+    L = max(m, 64) * 2 + 3
+    c, idx, q, sk, sv, rng = _draw(hq, hkv, dh, 32, 1, n_sink, m, L, B, dtype, 100 + m)
+    Dp = hkv * dh
+    kh, vh = (rng.standard_normal((B, m, Dp)).astype(np.float32) for _ in range(2))
+    f64 = lambda x: x.to(torch.float64).numpy()  # noqa: E731
+    pos = np.concatenate([np.broadcast_to(np.arange(n_sink), (B, n_sink)), n_sink + idx], axis=1)
+    ref = decode.attend(f64(q), np.concatenate([f64(sk), kh], axis=1), np.concatenate([f64(sv), vh], axis=1), pos,
+                        np.full(B, n_sink + L - 1), 10000.0, hkv)
+    ws = s4r.alloc_workspace(c)
+    g = lambda x: None if x.numel() == 0 else x.cuda()  # noqa: E731
+    args = (g(q), g(sk), g(sv), dev(idx.astype(np.int32), torch.int32), dev(kh, torch.float32), dev(vh, torch.float32))
+    out = s4r.sparse_attn(c, L, *args, ws)
+    again = s4r.sparse_attn(c, L, *args, ws)
+    torch.cuda.synchronize()
+    # fp32 logits of a few units over 128 products and a softmax of m terms: some 1e-6
+    err = rel_err_rows(out.cpu().numpy(), ref)
+    print(f"[rows] {hq}/{hkv} d{dh} m={m} {dtype}: err {err:.2e}", flush=True)
+    assert err < 3e-5
+    assert torch.equal(out, again)
+
+
+@pytest.mark.parametrize("hq,hkv,dh,rank,nb,m,B,dtype", [
+    (8, 2, 64, 32, 2, 5, 1, "fp32"), (8, 8, 128, 160, 1, 16, 2, "bf16"), (32, 8, 128, 204, 1, 17, 1, "bf16"),
+    (4, 4, 128, 192, 1, 100, 1, "fp32"), (16, 4, 64, 96, 2, 301, 2, "bf16"),
+])
+def test_reconstruction(hq, hkv, dh, rank, nb, m, B, dtype):
+    L = 2 * m + 40
+    c, idx, _, _, _, rng = _draw(hq, hkv, dh, rank, nb, 0, m, L, B, dtype, 7 * m)
+    dt, Dp = s4r.storage_dtype(c), hkv * dh
+    rnd = lambda *s: torch.from_numpy(rng.standard_normal(s)).to(dt)  # noqa: E731
+    bases = [rnd(B, nb, Dp // nb, rank) for _ in range(2)]
+    coefs = [rnd(B, c.capacity, nb * rank) for _ in range(2)]
+    pad = lambda x: s4r.pad_latent(x, rank, nb if x.shape[-1] == nb * rank else 1)  # noqa: E731
+    got = s4r.reconstruct(c, L, dev(idx.astype(np.int32), torch.int32),
+                          *[s4r.pad_latent(x, rank).cuda() for x in bases],
+                          *[s4r.pack_coef(c, c.capacity, pad(x).cuda()) for x in coefs])
+    torch.cuda.synchronize()
+    for out, basis, coef in zip(got, bases, coefs):
+        rows = np.stack([coef[b].to(torch.float64).numpy()[idx[b]] for b in range(B)])
+        ref = decode.reconstruct(rows, basis.to(torch.float64).numpy())
+        # up to 224 products of unit normals in fp32: some 1e-6 of a row's largest value
+        assert rel_err_rows(out.cpu().numpy(), ref) < 1e-5
