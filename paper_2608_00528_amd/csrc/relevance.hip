@@ -15,7 +15,9 @@ namespace s4r {
 // G <= 8 / 16.  The stream's exp values are stored token-major,
 // e[b][x][c] for query column c = g * W_q + i (GWP = G * W_q rounded up to a
 // multiple of 4, padding columns zero), with one reference per 16-token tile,
-// tref[b][tile][c].  One memory latency: the scoring workgroups' statistics,
+// tref[b][tile][c].  Reading the exp values bounds the large batches (8 x 128k
+// tokens at 7 columns: 33.5 MB, 8 us at the rate of a large copy), the chain
+// of dependent phases the small ones.  One memory latency: the scoring workgroups' statistics,
 // the chunk's tile references and its exp values (plus the pooling halo) are
 // all requested before any is used.  Then each wave folds query columns'
 // statistics into the global (M, S), sums in fp64 (the same fixed order in
@@ -26,8 +28,15 @@ namespace s4r {
 // column in every workgroup.  Per staged position the window mean
 // over the W_q rows is formed once (fp32 products of values exact to about an
 // ulp; the max-pooling that follows is exact), staged in LDS, and every thread
-// pools outputs t, t + 256, ... (consecutive lanes read consecutive words: no
-// bank conflicts) and sums the groups in fp64.
+// pools consecutive outputs, whose windows overlap (four outputs of a 7-wide
+// window read 12 values in three 16-byte reads instead of 28), and sums the
+// groups in fp64.  The wave reductions use DPP and lane swaps, the factors one
+// thread per (tile, column), and the groups are a loop: unrolled over groups,
+// outputs and window widths the kernel was up to 90 KB of code, more than the
+// instruction cache, which costs about 0.65 us per KB run through.  Measured
+// before and after: 19.2 -> 13.9 us (8 x 128k, 7 columns), 12.5 -> 9.8 (32 x
+// 32k, 4), 8.7 -> 6.9 (4 x 128k, 4), 14.6 -> 7.6 (16k, 16 columns of 4 rows),
+// 12.2 -> 9.9 (120k windowed).
 constexpr int kRelThreads = 256;
 // scoring-workgroup statistics per lane that the relevance kernel folds itself
 // (KSP, all requested together): 2 (up to 128 scoring workgroups), or 8 (up to
@@ -39,7 +48,6 @@ template <int NQ>
 constexpr int rel_stat_max() {
   return 64 * (NQ == 1 ? kRelStatWide : kRelStatPer);
 }
-constexpr int kRelMaxTiles = 1024 / kTileTok + 8;   // tiles touched by a chunk and its halo (h <= 32)
 
 // tokens per workgroup: 1024 (G <= 8) or 512, halved (down to 256) while the
 // grid would give fewer than four workgroups per CU.  Measured at 1024, 512
@@ -54,60 +62,110 @@ int relevance_chunk(const Problem& P, int64_t L) {
   return c;
 }
 
+// LDS row stride of one group's staged positions (16-byte rows; pool_aggregate
+// reads up to 3 values past the window of a chunk's last output)
+__host__ __device__ constexpr int rel_row(int span) { return (span + 7) / 4 * 4; }
+
 // Pooling (kappa = 2H + 1, stride 1, same length) and aggregation over the G
-// groups for outputs t, t + 256, ... of a chunk.  With H known at compile time
-// every window value is requested from LDS before any is combined, so the
-// reads overlap; H < 0 is the generic (slower) path for wide kernels.
-template <int H, int TPT, int GMAX>
-__device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int span, int t, int G, int kappa,
+// groups for outputs o0 .. o0 + TPT - 1 (o0 a multiple of TPT): the windows of
+// neighbouring outputs overlap, so a thread reads TPT + 2H values per group in
+// aligned vectors and shares the maximum of the common part.  H < 0 is the
+// generic path for wide kernels.
+template <int H, int TPT>
+__device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int row, int o0, int G, int kappa,
                                                int pool_mode, int agg, float (&af)[TPT]) {
-  const int h = (H >= 0) ? H : kappa / 2;
+  double acc[TPT];
 #pragma unroll
-  for (int j = 0; j < TPT; ++j) {
-    const int o = t + j * kRelThreads;                     // window of output o: vs[g][o .. o + 2h]
-    double acc = (agg == S4R_AGG_MEAN) ? 0.0 : -INFINITY;
-    if constexpr (H >= 0) {
-      float w[GMAX][2 * (H > 0 ? H : 0) + 1];
+  for (int j = 0; j < TPT; ++j) acc[j] = (agg == S4R_AGG_MEAN) ? 0.0 : -INFINITY;
+  const bool mean = agg == S4R_AGG_MEAN;
+  if constexpr (H >= 0) {
+    constexpr int NV = (TPT + 2 * H + TPT - 1) / TPT * TPT;
+#pragma unroll 4
+    for (int g = 0; g < G; ++g) {
+      const float* p = vs + g * row + o0;
+      float w[NV];
 #pragma unroll
-      for (int g = 0; g < GMAX; ++g)
+      for (int i = 0; i < NV; i += TPT) {
+        if constexpr (TPT == 4)
+          *reinterpret_cast<float4*>(&w[i]) = *reinterpret_cast<const float4*>(p + i);
+        else if constexpr (TPT == 2)
+          *reinterpret_cast<float2*>(&w[i]) = *reinterpret_cast<const float2*>(p + i);
+        else
+          w[i] = p[i];
+      }
+      float a[TPT];
+      if (pool_mode == S4R_POOL_MAX) {
+        if constexpr (2 * H >= TPT - 1) {
+          float m = w[TPT - 1];                    // in every output's window
 #pragma unroll
-        for (int d = 0; d <= 2 * H; ++d) w[g][d] = vs[min(g, G - 1) * span + o + d];   // unguarded: overlapped
+          for (int d = TPT; d <= 2 * H; ++d) m = fmaxf(m, w[d]);
 #pragma unroll
-      for (int g = 0; g < GMAX; ++g) {
-        if (g < G) {
-          float a;
-          if (pool_mode == S4R_POOL_MAX) {
-            a = w[g][0];
+          for (int j = 0; j < TPT; ++j) {
+            float x = m;
 #pragma unroll
-            for (int d = 1; d <= 2 * H; ++d) a = fmaxf(a, w[g][d]);
-          } else {
-            double sa = 0.0;
+            for (int d = j; d < TPT - 1; ++d) x = fmaxf(x, w[d]);
 #pragma unroll
-            for (int d = 0; d <= 2 * H; ++d) sa += (double)w[g][d];
-            a = (float)(sa / kappa);
+            for (int d = 2 * H + 1; d <= j + 2 * H; ++d) x = fmaxf(x, w[d]);
+            a[j] = x;
           }
-          acc = (agg == S4R_AGG_MEAN) ? acc + (double)a : fmax(acc, (double)a);
+        } else {
+#pragma unroll
+          for (int j = 0; j < TPT; ++j) {
+            a[j] = w[j];
+#pragma unroll
+            for (int d = 1; d <= 2 * H; ++d) a[j] = fmaxf(a[j], w[j + d]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < TPT; ++j) {
+          double sa = 0.0;
+#pragma unroll
+          for (int d = 0; d <= 2 * H; ++d) sa += (double)w[j + d];
+          a[j] = (float)(sa / kappa);
         }
       }
-    } else {
+#pragma unroll
+      for (int j = 0; j < TPT; ++j) acc[j] = mean ? acc[j] + (double)a[j] : fmax(acc[j], (double)a[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < TPT; ++j)
       for (int g = 0; g < G; ++g) {
-        const float* v = vs + g * span + o;
+        const float* v = vs + g * row + o0 + j;
         float a = v[0];
         double sa = (double)v[0];
-        for (int d = 1; d <= 2 * h; ++d) {
+        for (int d = 1; d < kappa; ++d) {
           a = fmaxf(a, v[d]);
           sa += (double)v[d];
         }
         if (pool_mode != S4R_POOL_MAX) a = (float)(sa / kappa);
-        acc = (agg == S4R_AGG_MEAN) ? acc + (double)a : fmax(acc, (double)a);
+        acc[j] = mean ? acc[j] + (double)a : fmax(acc[j], (double)a);
       }
-    }
-    af[j] = (float)((agg == S4R_AGG_MEAN) ? acc / G : acc);
+  }
+#pragma unroll
+  for (int j = 0; j < TPT; ++j) af[j] = (float)(mean ? acc[j] / G : acc[j]);
+}
+
+template <int TPT>
+__device__ __forceinline__ void pool_dispatch(const float* vs, int row, int o0, int G, int kappa, int pool_mode, int agg,
+                                              float (&af)[TPT]) {
+  switch (kappa / 2) {
+    case 0: pool_aggregate<0, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 1: pool_aggregate<1, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 2: pool_aggregate<2, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 3: pool_aggregate<3, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 4: pool_aggregate<4, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    default: pool_aggregate<-1, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
   }
 }
 
-// WIN (windowed step, query window of wrows rows): the stream scored only
-// the newest query row (its G columns, Wq = 1 here); the softmax of each
+// what the kernel's query columns are: one query row per group, several, or
+// the newest row of a windowed step
+enum RelMode { kRelOne, kRelRows, kRelWindow };
+
+// kRelWindow (windowed step, query window of wrows rows): the stream scored
+// only the newest query row (its G columns, Wq = 1 here); the softmax of each
 // older row over its own keys comes from the window state
 // [B][wrows][G][cap], row slot L_r mod wrows for the row that was newest at
 // length L_r (it covers keys < L_r).  This kernel adds the newest row's
@@ -116,8 +174,11 @@ __device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int
 // is kept in fp64 as well, in two buffers [2][B][G][cap] by the parity of L:
 // the step reads buffer L & 1 and writes buffer (L + 1) & 1 = that sum plus
 // the newest row minus the row leaving the window (the one newest at
-// L - wrows + 1, masked at its key limit), for the positions it owns.
-template <int NQ, int TPT, bool WQ1, bool WIN, int KSP>
+// L - wrows + 1, masked at its key limit), for the positions it owns.  Without
+// one (up to kWinDirectRows rows) the older rows are read directly, four
+// positions of a group per unit.  In the 256-token chunks of a small batch
+// either is requested with the first loads.
+template <int NQ, int TPT, int MODE, int KSP>
 __global__ __launch_bounds__(kRelThreads) void k_relevance(
     const float* __restrict__ e, const float* __restrict__ tref, const double* __restrict__ wg_stats,
     const double* __restrict__ col_stats, float* __restrict__ atilde, uint32_t* __restrict__ hist, float* __restrict__ scores_out,
@@ -125,8 +186,12 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
     Lens lens, int key_shift, float* __restrict__ state, int wrows, double* __restrict__ rsum, int hist_nc) {
   constexpr int GWP = 4 * NQ;
   constexpr int CHUNK = kRelThreads * TPT;
-  constexpr int SPAN_MAX = CHUNK + 64;
-  constexpr int PPT = (SPAN_MAX + kRelThreads - 1) / kRelThreads;   // staged positions per thread
+  constexpr int PPT = TPT + 1;                             // staged positions per thread (span <= CHUNK + 64)
+  constexpr int NTL = CHUNK / kTileTok + 6;                // tiles of a chunk and its halo
+  constexpr int FPT = (NTL * GWP + kRelThreads - 1) / kRelThreads;
+  constexpr bool WIN = MODE == kRelWindow;
+  constexpr bool WIN_PRE = WIN && TPT == 1 && NQ == 1;     // older rows with the first loads
+  constexpr int UPRE = 2;                                  // units of older rows per thread held ahead
   const int b = blockIdx.y;
   const int score_stride = L;                      // scores_out rows are [B, L] with the call's (largest) L
   {                                                // this sequence's length (ragged batch: n_hist shifts with it)
@@ -134,25 +199,26 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
     n_hist += Lb - L;
     L = Lb;
   }
-  if ((int)blockIdx.x * kRelThreads * TPT >= L) return;   // past this sequence's end
+  if ((int)blockIdx.x * CHUNK >= L) return;                // past this sequence's end
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int GW = G * Wq;
   const int h = kappa / 2;
   const int t0 = blockIdx.x * CHUNK;
   const int x0 = t0 - h;                                   // first staged position
   const int span = CHUNK + 2 * h;
+  const int row = rel_row(span);
   const int tile_lo = max(x0, 0) / kTileTok;
   const int tile_hi = (min(t0 + CHUNK + h, L) - 1) / kTileTok;
-  const int ntl = tile_hi - tile_lo + 1;                   // <= kRelMaxTiles
+  const int nfac = (tile_hi - tile_lo + 1) * GWP;          // <= NTL * GWP
 
   __shared__ uint32_t hl[kHistBins];
   __shared__ double sM[GWP], sInvS[GWP];
-  __shared__ float fac[kRelMaxTiles][GWP];                 // exp(ref - M) / S per tile and column
-  extern __shared__ float vs[];                            // [G][span]: window mean at x0 + i
+  __shared__ __align__(16) float fac[NTL * GWP];           // exp(ref - M) / S per tile and column
+  extern __shared__ __align__(16) float vs[];              // [G][row]: window mean at x0 + i
 
   // ---- all global reads of this workgroup, issued before any is used ----------
-  // statistics: wave w folds columns w, w + 4, ...; two batches of 64 lanes in flight
-  // (or, with many scoring workgroups, the global statistics k_fold_stats formed)
+  // statistics: wave w folds columns w, w + 4, .., KSP entries per lane (or,
+  // with many scoring workgroups, the global statistics k_fold_stats formed)
   double2 st[NQ][KSP];
   const double2* stats = reinterpret_cast<const double2*>(wg_stats) + (int64_t)b * GW * nwg;
   double2 cs = make_double2(0.0, 0.0);
@@ -166,21 +232,67 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
       for (int k = 0; k < KSP; ++k) st[q][k] = stats[(int64_t)c * nwg + min(lane + 64 * k, nwg - 1)];
     }
   }
-  // tile references: thread t loads tile tile_lo + t (all columns)
-  float4 rf[NQ];
+  // tile references, contiguous over (tile, column)
+  float rf[FPT];
   {
-    const float4* tp = reinterpret_cast<const float4*>(tref + ((int64_t)b * ntiles_cap + tile_lo + min(t, ntl - 1)) * GWP);
+    const float* tp = tref + ((int64_t)b * ntiles_cap + tile_lo) * GWP;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) rf[q] = tp[q];
+    for (int k = 0; k < FPT; ++k) rf[k] = tp[min(t + k * kRelThreads, nfac - 1)];
   }
-  // exp values of the staged positions (clamped into [0, L); masked later)
+  // exp values of the staged positions (clamped into the span and [0, L); masked later)
   float4 ev[PPT][NQ];
 #pragma unroll
   for (int k = 0; k < PPT; ++k) {
-    const int x = min(max(x0 + t + k * kRelThreads, 0), L - 1);
+    const int x = min(max(x0 + min(t + k * kRelThreads, span - 1), 0), L - 1);
     const float4* ep = reinterpret_cast<const float4*>(e + ((int64_t)b * cap + x) * GWP);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) ev[k][q] = ep[q];
+  }
+  // the window state: running sum and leaving row per staged position, or
+  // units of older rows
+  float* sb = WIN ? state + (int64_t)b * wrows * G * cap : nullptr;
+  const double* scur = nullptr;
+  double* snext = nullptr;
+  const float* sold = nullptr;
+  const int Lo = L - wrows + 1;                            // the leaving row was newest at Lo
+  double so[WIN_PRE ? PPT : 1][GWP];
+  float po[WIN_PRE ? PPT : 1][GWP];
+  const int u0 = (x0 >= 0 ? x0 : x0 - 3) / 4;              // floor(x0 / 4)
+  const int nu = (x0 + span + 3) / 4 - u0;                 // units covering the staged positions
+  float4 old[WIN_PRE ? UPRE : 1][kWinDirectRows - 1];
+  // the older rows (ages 1 .. wrows - 1, slot (L - a) mod wrows) of unit w
+  auto load_unit = [&](int w, float4 (&o)[kWinDirectRows - 1]) __attribute__((always_inline)) {
+    const int g = w / nu;
+    const int xl = min(max(4 * (u0 + w % nu), 0), (int)(cap - 4));
+#pragma unroll
+    for (int v = 0; v < kWinDirectRows - 1; ++v) {
+      const int a = min(1 + v, wrows - 1);
+      const int slot = ((L - a) % wrows + wrows) % wrows;  // L - a < 0 early on: masked
+      o[v] = *reinterpret_cast<const float4*>(sb + ((int64_t)slot * G + g) * cap + xl);
+    }
+  };
+  if constexpr (WIN) {
+    if (rsum) {
+      scur = rsum + ((int64_t)(L & 1) * gridDim.y + b) * G * cap;
+      snext = rsum + ((int64_t)((L + 1) & 1) * gridDim.y + b) * G * cap;
+      sold = sb + (int64_t)((Lo % wrows + wrows) % wrows) * G * cap;
+    }
+    if constexpr (WIN_PRE) {
+      if (rsum) {
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+          const int x = min(max(x0 + min(t + k * kRelThreads, span - 1), 0), (int)cap - 1);
+#pragma unroll
+          for (int c = 0; c < GWP; ++c) {
+            so[k][c] = scur[(int64_t)min(c, G - 1) * cap + x];
+            po[k][c] = sold[(int64_t)min(c, G - 1) * cap + x];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < UPRE; ++i) load_unit(min(t + i * kRelThreads, G * nu - 1), old[i]);
+      }
+    }
   }
   for (int i = t; i < kHistBins; i += kRelThreads) hl[i] = 0;
 
@@ -190,61 +302,38 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
       sM[t] = cs.x;
       sInvS[t] = cs.y;
     }
-  }
+  } else {                                                 // nwg <= 64 * KSP
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int c = wave + 4 * q;
-    if (!col_stats && c < GW) {                            // wave-uniform
-      const double* srow = wg_stats + ((int64_t)b * GW + c) * nwg * 2;
-      double M = -INFINITY, S = 0.0;
-      for (int base = 0; base < nwg; base += 64 * KSP) {
-        double2 s2[KSP];
+    for (int q = 0; q < NQ; ++q) {
+      const int c = wave + 4 * q;
+      if (c < GW) {                                        // wave-uniform
+        float m = -INFINITY;                               // maxima are fp32 values
 #pragma unroll
-        for (int k = 0; k < KSP; ++k) {
-          if (base == 0) {
-            s2[k] = st[q][k];
-          } else {                                         // more than 128 scoring workgroups
-            const int w = min(base + lane + 64 * k, nwg - 1);
-            s2[k] = make_double2(srow[2 * w], srow[2 * w + 1]);
-          }
-        }
-        double m = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < KSP; ++k)
-          if (base + lane + 64 * k < nwg) m = fmax(m, s2[k].x);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmax(m, shfl_xor_d(m, o));
+        for (int k = 0; k < KSP; ++k) m = fmaxf(m, lane + 64 * k < nwg ? (float)st[q][k].x : -INFINITY);
+        m = wave_max(m);
         double s = 0.0;
 #pragma unroll
-        for (int k = 0; k < KSP; ++k)
-          if (base + lane + 64 * k < nwg && s2[k].x != -INFINITY) s += s2[k].y * (double)exp_neg_accurate(s2[k].x - m);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += shfl_xor_d(s, o);
-        if (m != -INFINITY) {
-          const double Mn = fmax(M, m);
-          S = ((M == -INFINITY) ? 0.0 : S * (double)exp_neg_accurate(M - Mn)) + s * (double)exp_neg_accurate(m - Mn);
-          M = Mn;
+        for (int k = 0; k < KSP; ++k) {
+          const bool live = lane + 64 * k < nwg && st[q][k].x != -INFINITY;
+          const double x = st[q][k].y * (double)exp_neg_accurate(live ? st[q][k].x - (double)m : 0.0);
+          s += live ? x : 0.0;
         }
-      }
-      if (lane == 0) {
-        sM[c] = M;
-        sInvS[c] = 1.0 / S;
+        s = wave_sum(s);
+        if (lane == 0) {
+          sM[c] = (double)m;
+          sInvS[c] = 1.0 / s;
+        }
       }
     }
   }
   __syncthreads();
   // ---- per-tile factors ---------------------------------------------------------------
-  if (t < ntl) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const float r4[4] = {rf[q].x, rf[q].y, rf[q].z, rf[q].w};
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = 4 * q + u;
-        fac[t][c] = (c < GW && r4[u] != -INFINITY)
-                        ? (float)((double)exp_neg_accurate((double)r4[u] - sM[c]) * sInvS[c]) : 0.f;
-      }
-    }
+  for (int k = 0; k < FPT; ++k) {
+    const int i = t + k * kRelThreads, c = i % GWP;
+    if (i < nfac)
+      fac[i] = (c < GW && rf[k] != -INFINITY)
+                   ? (float)((double)exp_neg_accurate((double)rf[k] - sM[c]) * sInvS[c]) : 0.f;
   }
   __syncthreads();
   // ---- window mean over the W_q rows of every staged position -------------------------
@@ -256,124 +345,114 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
     if (i < span) {
       const int x = x0 + i;
       const bool in = x >= 0 && x < L;
-      const float* fr = fac[min(max(x, 0), L - 1) / kTileTok - tile_lo];
-      float ex[GWP];
+      const float* fr = fac + (min(max(x, 0), L - 1) / kTileTok - tile_lo) * GWP;
+      float ex[GWP];                                       // the probabilities
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        ex[4 * q] = ev[k][q].x;
-        ex[4 * q + 1] = ev[k][q].y;
-        ex[4 * q + 2] = ev[k][q].z;
-        ex[4 * q + 3] = ev[k][q].w;
+        const float4 f4 = *reinterpret_cast<const float4*>(fr + 4 * q);
+        ex[4 * q] = ev[k][q].x * f4.x;
+        ex[4 * q + 1] = ev[k][q].y * f4.y;
+        ex[4 * q + 2] = ev[k][q].z * f4.z;
+        ex[4 * q + 3] = ev[k][q].w * f4.w;
       }
       if constexpr (WIN) {
         // the newest row's softmax: into its slot (own chunk) and into LDS;
         // the older rows are added from the running sum, else below
-        float* sb = state + (int64_t)b * wrows * G * cap;
-        const int slot_new = L % wrows;
         const bool own = in && x >= t0 && x < t0 + CHUNK;
-        if (rsum) {
-          const double* scur = rsum + ((int64_t)(L & 1) * gridDim.y + b) * G * cap;
-          double* snext = rsum + ((int64_t)((L + 1) & 1) * gridDim.y + b) * G * cap;
-          const int Lo = L - wrows + 1;                        // the leaving row was newest at Lo
-          const float* sold = sb + (int64_t)((Lo % wrows + wrows) % wrows) * G * cap;
-          const int xc = min(max(x, 0), (int)cap - 1);
+        float* snew = sb + (int64_t)(L % wrows) * G * cap;
+        const int xc = min(max(x, 0), (int)cap - 1);
 #pragma unroll
-          for (int c = 0; c < GWP; ++c) {
-            if (c < G) {
-              const float pn = in ? ex[c] * fr[c] : 0.f;
-              const double so = scur[(int64_t)c * cap + xc];
-              const float po = sold[(int64_t)c * cap + xc];
-              if (own) {
-                sb[((int64_t)slot_new * G + c) * cap + x] = pn;
-                snext[(int64_t)c * cap + x] = (so + (double)pn) - (x < Lo ? (double)po : 0.0);
-              }
-              vs[c * span + i] = in ? (float)((so + (double)pn) * (double)inv_wq) : pad;
+        for (int c = 0; c < GWP; ++c) {
+          if (c < G) {
+            const float pn = in ? ex[c] : 0.f;
+            if (own) snew[(int64_t)c * cap + x] = pn;
+            float v = pn;
+            if (rsum) {
+              const double s0 = WIN_PRE ? so[WIN_PRE ? k : 0][c] : scur[(int64_t)c * cap + xc];
+              const float p0 = WIN_PRE ? po[WIN_PRE ? k : 0][c] : sold[(int64_t)c * cap + xc];
+              const double sn = s0 + (double)pn;
+              if (own) snext[(int64_t)c * cap + x] = sn - (x < Lo ? (double)p0 : 0.0);
+              v = in ? (float)(sn * (double)inv_wq) : pad;
             }
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < GWP; ++c) {
-            if (c < G) {
-              const float pn = in ? ex[c] * fr[c] : 0.f;
-              if (own) sb[((int64_t)slot_new * G + c) * cap + x] = pn;
-              vs[c * span + i] = pn;
-            }
+            vs[c * row + i] = v;
           }
         }
-      } else if constexpr (WQ1) {
+      } else if constexpr (MODE == kRelOne) {
 #pragma unroll
         for (int c = 0; c < GWP; ++c)
-          if (c < G) vs[c * span + i] = in ? ex[c] * fr[c] : pad;
+          if (c < G) vs[c * row + i] = in ? ex[c] : pad;
       } else {
-        for (int g = 0; g < G; ++g) {
-          float sum = 0.f;
+        // columns g * Wq .. (g + 1) * Wq - 1 are group g's rows
+        float sum = 0.f;
+        int left = Wq, g = 0;                              // uniform
 #pragma unroll
-          for (int c = 0; c < GWP; ++c)
-            if (c >= g * Wq && c < (g + 1) * Wq) sum += ex[c] * fr[c];
-          vs[g * span + i] = in ? sum * inv_wq : pad;
+        for (int c = 0; c < GWP; ++c) {
+          if (g < G) {
+            sum += ex[c];
+            if (--left == 0) {
+              vs[g * row + i] = in ? sum * inv_wq : pad;
+              sum = 0.f;
+              left = Wq;
+              ++g;
+            }
+          }
         }
       }
     }
   }
   __syncthreads();
-  if (WIN && !rsum) {
-    // ---- older rows of the window: row of age a = 1 .. wrows - 1 covers keys
-    // < L - a, in slot (L - a) mod wrows.  Unit u = four consecutive positions
-    // 4 (u0 + u) .. + 3 (16-byte loads, unconditional at clamped positions,
-    // masked after) of group g; eight rows in flight per batch
-    const float* sb = state + (int64_t)b * wrows * G * cap;
-    const int u0 = (x0 >= 0 ? x0 : x0 - 3) / 4;         // floor(x0 / 4)
-    const int nu = (x0 + span + 3) / 4 - u0;             // units covering the staged positions
-    for (int w = t; w < G * nu; w += kRelThreads) {
-      const int g = w / nu, xu = 4 * (u0 + w % nu);      // first position of the unit
-      const int xl = min(max(xu, 0), (int)(cap - 4));
-      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int a0 = 1; a0 < wrows; a0 += 8) {
-        float4 o[8];
+  if constexpr (WIN) {
+    if (!rsum) {                                           // (uniform: a kernel argument)
+      // older rows: the row of age a covers keys < L - a
+      auto add_unit = [&](int w, const float4 (&o)[kWinDirectRows - 1]) __attribute__((always_inline)) {
+        const int g = w / nu, xu = 4 * (u0 + w % nu);      // first position of the unit
+        const int xl = min(max(xu, 0), (int)(cap - 4));
+        float sv[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const int a = min(a0 + v, wrows - 1);
-          const int slot = ((L - a) % wrows + wrows) % wrows;   // L - a < 0 early on: masked below
-          o[v] = *reinterpret_cast<const float4*>(sb + ((int64_t)slot * G + g) * cap + xl);
+        for (int v = 0; v < kWinDirectRows - 1; ++v) {
+          const int lim = 1 + v < wrows ? L - (1 + v) : 0;   // keys of this row
+          const float o4[4] = {o[v].x, o[v].y, o[v].z, o[v].w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sv[j] += xl + j < lim ? o4[j] : 0.f;
         }
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const int lim = L - (a0 + v);                  // keys of this row
-          if (a0 + v < wrows) {
-            if (xl + 0 < lim) sum.x += o[v].x;
-            if (xl + 1 < lim) sum.y += o[v].y;
-            if (xl + 2 < lim) sum.z += o[v].z;
-            if (xl + 3 < lim) sum.w += o[v].w;
+        for (int j = 0; j < 4; ++j) {
+          const int x = xu + j, i = x - x0;
+          if (i >= 0 && i < span) {
+            const bool in = x >= 0 && x < L && xl == xu;
+            vs[g * row + i] = in ? (vs[g * row + i] + sv[j]) * inv_wq : pad;
           }
         }
-      }
-      const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
+      };
+      int w = t;
+      if constexpr (WIN_PRE) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int x = xu + j, i = x - x0;
-        if (i >= 0 && i < span) {
-          const bool in = x >= 0 && x < L && xl == xu;
-          vs[g * span + i] = in ? (vs[g * span + i] + sv[j]) * inv_wq : pad;
-        }
+        for (int i = 0; i < UPRE; ++i, w += kRelThreads)
+          if (w < G * nu) add_unit(w, old[i]);
       }
+      for (; w < G * nu; w += kRelThreads) {
+        float4 o[kWinDirectRows - 1];
+        load_unit(w, o);
+        add_unit(w, o);
+      }
+      __syncthreads();
     }
-    __syncthreads();                                       // (wave-uniform: rsum is a kernel argument)
   }
   // ---- pooling (kappa, stride 1, same length) and aggregation over G -------------------
   float af[TPT];
-  switch (h) {
-    case 0: pool_aggregate<0, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 1: pool_aggregate<1, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 2: pool_aggregate<2, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 3: pool_aggregate<3, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 4: pool_aggregate<4, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    default: pool_aggregate<-1, TPT, GWP>(vs, span, t, G, kappa, pool_mode, agg, af); break;
+  pool_dispatch<TPT>(vs, row, t * TPT, G, kappa, pool_mode, agg, af);
+  const int xo = t0 + t * TPT;
+  float* ap = atilde + (int64_t)b * cap + xo;              // cap is a multiple of 16: aligned for TPT values
+  if constexpr (TPT == 4) {
+    if (xo + 3 < L) *reinterpret_cast<float4*>(ap) = make_float4(af[0], af[1], af[2], af[3]);
+  } else if constexpr (TPT == 2) {
+    if (xo + 1 < L) *reinterpret_cast<float2*>(ap) = make_float2(af[0], af[1]);
   }
 #pragma unroll
   for (int j = 0; j < TPT; ++j) {
-    const int x = t0 + t + j * kRelThreads;
+    const int x = xo + j;
     if (x < L) {
-      atilde[(int64_t)b * cap + x] = af[j];
+      if (TPT == 1 || xo + TPT > L) ap[j] = af[j];
       if (scores_out) scores_out[(int64_t)b * score_stride + x] = af[j];
     }
     if (x < n_hist) atomicAdd(&hl[selection_key_shift(af[j], key_shift) >> kHistShift], 1u);
@@ -398,7 +477,6 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
 constexpr int kWideChunk = kRelThreads;
 constexpr int kWideMaxTiles = (kWideChunk + 64) / kTileTok + 2;
 
-template <int GMAX>
 __global__ __launch_bounds__(kRelThreads) void k_relevance_wide(
     const float* __restrict__ e, const float* __restrict__ tref, const double* __restrict__ col_stats,
     float* __restrict__ atilde, uint32_t* __restrict__ hist, float* __restrict__ scores_out, int64_t cap, int L,
@@ -418,13 +496,14 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance_wide(
   const int t0 = blockIdx.x * kWideChunk;
   const int x0 = t0 - h;
   const int span = kWideChunk + 2 * h;
+  const int row = rel_row(span);
   const int tile_lo = max(x0, 0) / kTileTok;
   const int tile_hi = (min(t0 + kWideChunk + h, L) - 1) / kTileTok;
   const int ntl = tile_hi - tile_lo + 1;                   // <= kWideMaxTiles
 
   __shared__ uint32_t hl[kHistBins];
   __shared__ __align__(16) float fac[kWideMaxTiles * kMaxGW];   // [tile][column]
-  extern __shared__ float vs[];                            // [G][span]
+  extern __shared__ __align__(16) float vs[];              // [G][row]
   for (int i = t; i < kHistBins; i += kRelThreads) hl[i] = 0;
   const double2* cs = reinterpret_cast<const double2*>(col_stats) + (int64_t)b * GW;
   for (int i = t; i < ntl * GW; i += kRelThreads) {
@@ -458,18 +537,11 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance_wide(
       }
       v = (float)(sum * inv_wq);
     }
-    vs[g * span + xi] = v;
+    vs[g * row + xi] = v;
   }
   __syncthreads();
   float af[1];
-  switch (h) {
-    case 0: pool_aggregate<0, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 1: pool_aggregate<1, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 2: pool_aggregate<2, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 3: pool_aggregate<3, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    case 4: pool_aggregate<4, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-    default: pool_aggregate<-1, 1, GMAX>(vs, span, t, G, kappa, pool_mode, agg, af); break;
-  }
+  pool_dispatch<1>(vs, row, t, G, kappa, pool_mode, agg, af);
   const int x = t0 + t;
   if (x < L) {
     atilde[(int64_t)b * cap + x] = af[0];
@@ -554,15 +626,15 @@ template <int NQ, int TPT>
 static void launch_rel_t(const Problem& P, const Workspace& ws, int64_t L, float* scores_out, hipStream_t st) {
   const int n_hist = (int)std::max<int64_t>(L - P.W, 0);
   constexpr int chunk = kRelThreads * TPT;
-  const size_t lds = (size_t)P.G * (chunk + 2 * (P.kappa / 2)) * sizeof(float);
+  const size_t lds = (size_t)P.G * rel_row(chunk + 2 * (P.kappa / 2)) * sizeof(float);
   dim3 grid((unsigned)((L + chunk - 1) / chunk), P.B);
   const int nwg = score_workgroups(P, L);
   const bool fold = nwg > rel_stat_max<NQ>();
   constexpr int KW = NQ == 1 ? kRelStatWide : kRelStatPer;   // (only one column per wave folds 512)
   auto kern = nwg > 64 * kRelStatPer && !fold
-                  ? (P.Wq == 1 ? k_relevance<NQ, TPT, true, false, KW> : k_relevance<NQ, TPT, false, false, KW>)
-                  : (P.Wq == 1 ? k_relevance<NQ, TPT, true, false, kRelStatPer>
-                               : k_relevance<NQ, TPT, false, false, kRelStatPer>);
+                  ? (P.Wq == 1 ? k_relevance<NQ, TPT, kRelOne, KW> : k_relevance<NQ, TPT, kRelRows, KW>)
+                  : (P.Wq == 1 ? k_relevance<NQ, TPT, kRelOne, kRelStatPer>
+                               : k_relevance<NQ, TPT, kRelRows, kRelStatPer>);
   if (fold) hipLaunchKernelGGL(k_fold_stats, dim3(P.GW, P.B), dim3(256), 0, st, ws.wg_stats, ws.col_stats, P.GW, nwg);
   hipLaunchKernelGGL(kern, grid, dim3(kRelThreads), lds, st, ws.e, ws.run_m, ws.wg_stats,
                      fold ? ws.col_stats : nullptr, ws.atilde, ws.hist, scores_out, P.cap, (int)L, n_hist, P.G, P.Wq, P.kappa, P.pool_mode, P.agg,
@@ -584,10 +656,9 @@ static void launch_rel_wide(const Problem& P, const Workspace& ws, int64_t L, fl
   const int n_hist = (int)std::max<int64_t>(L - P.W, 0);
   const int nwg = score_workgroups(P, L);
   hipLaunchKernelGGL(k_fold_stats, dim3(P.GW, P.B), dim3(256), 0, st, ws.wg_stats, ws.col_stats, P.GW, nwg);
-  const size_t lds = (size_t)P.G * (kWideChunk + 2 * (P.kappa / 2)) * sizeof(float);
+  const size_t lds = (size_t)P.G * rel_row(kWideChunk + 2 * (P.kappa / 2)) * sizeof(float);
   dim3 grid((unsigned)((L + kWideChunk - 1) / kWideChunk), P.B);
-  auto kern = P.G <= 4 ? k_relevance_wide<4> : (P.G <= 8 ? k_relevance_wide<8> : k_relevance_wide<16>);
-  hipLaunchKernelGGL(kern, grid, dim3(kRelThreads), lds, st, ws.e, ws.run_m, ws.col_stats, ws.atilde, ws.hist,
+  hipLaunchKernelGGL(k_relevance_wide, grid, dim3(kRelThreads), lds, st, ws.e, ws.run_m, ws.col_stats, ws.atilde, ws.hist,
                      scores_out, P.cap, (int)L, n_hist, P.G, P.Wq, gw_padded(P), P.kappa, P.pool_mode, P.agg,
                      (int)(P.cap / kTileTok), P.lens, fused_key_shift(P, L), hist_copies(grid.x));
 }
@@ -611,14 +682,14 @@ static void launch_rel_win_t(const Problem& P1, const Workspace& ws, int64_t L, 
                              int wrows, hipStream_t st) {
   const int n_hist = (int)std::max<int64_t>(L - P1.W, 0);
   constexpr int chunk = kRelThreads * TPT;
-  const size_t lds = (size_t)P1.G * (chunk + 2 * (P1.kappa / 2)) * sizeof(float);
+  const size_t lds = (size_t)P1.G * rel_row(chunk + 2 * (P1.kappa / 2)) * sizeof(float);
   dim3 grid((unsigned)((L + chunk - 1) / chunk), P1.B);
   const int nwg = score_workgroups(P1, L);
   const bool fold = nwg > rel_stat_max<NQ>();
   if (fold) hipLaunchKernelGGL(k_fold_stats, dim3(P1.GW, P1.B), dim3(256), 0, st, ws.wg_stats, ws.col_stats, P1.GW, nwg);
   constexpr int KW = NQ == 1 ? kRelStatWide : kRelStatPer;
-  auto kern = nwg > 64 * kRelStatPer && !fold ? k_relevance<NQ, TPT, true, true, KW>
-                                              : k_relevance<NQ, TPT, true, true, kRelStatPer>;
+  auto kern = nwg > 64 * kRelStatPer && !fold ? k_relevance<NQ, TPT, kRelWindow, KW>
+                                              : k_relevance<NQ, TPT, kRelWindow, kRelStatPer>;
   hipLaunchKernelGGL(kern, grid, dim3(kRelThreads), lds, st, ws.e, ws.run_m, ws.wg_stats,
                      fold ? ws.col_stats : nullptr, ws.atilde, ws.hist, scores_out, P1.cap, (int)L, n_hist, P1.G, 1,
                      P1.kappa, P1.pool_mode, P1.agg, (int)(P1.cap / kTileTok), nwg, P1.lens, fused_key_shift(P1, L),

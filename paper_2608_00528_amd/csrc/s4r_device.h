@@ -174,6 +174,36 @@ __device__ __forceinline__ float slot_sum16(float x) {
   return x;
 }
 
+// the same over all 64 lanes (every lane gets the result): the gfx950 lane
+// swaps of a value with itself leave the two halves (even / odd rows) of it in
+// the two results; a few cycles per step where a permute through LDS takes
+// over a hundred
+__device__ __forceinline__ float wave_max(float x) {
+  x = slot_max16(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double x) {
+  x += dpp_d<0xB1>(x);
+  x += dpp_d<0x4E>(x);
+  x += dpp_d<0x124>(x);
+  x += dpp_d<0x128>(x);
+  const auto al = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+  const auto ah = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+  x = __hiloint2double(ah[0], al[0]) + __hiloint2double(ah[1], al[1]);
+  const auto bl = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+  const auto bh = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+  return __hiloint2double(bh[0], bl[0]) + __hiloint2double(bh[1], bl[1]);
+}
+
 // Workgroup barrier for LDS exchange only: waits for this wave's LDS traffic
 // (lgkmcnt) but not for outstanding global loads (vmcnt), so prefetched
 // global data stays in flight across the barrier.  (__syncthreads() waits for
