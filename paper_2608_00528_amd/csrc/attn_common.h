@@ -7,21 +7,6 @@
 
 namespace s4r {
 
-// RoPE angle of `pos` at frequency index f: returns cos / sin.  The angle is
-// pos * theta^(-2f/d_h); it is reduced in fp64 revolutions and evaluated
-// with the hardware sine / cosine (argument in revolutions).
-__device__ __forceinline__ double rope_rev_freq(float theta, int f, int dh) {
-  if (theta == 0.f) return 0.0;
-  return exp2(-2.0 * f / dh * log2((double)theta)) * 0.15915494309189535;  // / (2 pi)
-}
-__device__ __forceinline__ void rope_cs(int64_t pos, double rev_freq, float& c, float& s) {
-  double a = (double)pos * rev_freq;
-  a -= floor(a);
-  const float x = (float)a;
-  c = __builtin_amdgcn_cosf(x);
-  s = __builtin_amdgcn_sinf(x);
-}
-
 // RoPE phase of integer position pos at a frequency given as a 0.64
 // fixed-point number of revolutions per position: the fractional revolution
 // pos * F mod 1 is exact in 64-bit integer arithmetic
@@ -52,22 +37,38 @@ __device__ __forceinline__ void rope_freqs_fixed(double ratio, int f0, uint64_t 
   }
 }
 
-// operand loaders: 8 consecutive elements -> bf16 parts
+// operand loaders: 8 consecutive elements -> bf16 parts (Raw: the elements as
+// stored, split when they are used)
 template <typename T>
 struct Parts;
 template <>
 struct Parts<uint16_t> {
   static constexpr int n = 1;
+  struct Raw {
+    uint4 u;
+  };
+  __device__ __forceinline__ static void load_raw(const uint16_t* p, Raw& r) { r.u = *reinterpret_cast<const uint4*>(p); }
+  __device__ __forceinline__ static void split(const Raw& r, Op8* o) { o[0].u = r.u; }
   __device__ __forceinline__ static void load(const uint16_t* p, Op8* o) { o[0].u = *reinterpret_cast<const uint4*>(p); }
 };
 template <>
 struct Parts<float> {
   static constexpr int n = 3;
-  __device__ __forceinline__ static void load(const float* p, Op8* o) {
-    float x[8];
-    *reinterpret_cast<float4*>(&x[0]) = *reinterpret_cast<const float4*>(p);
-    *reinterpret_cast<float4*>(&x[4]) = *reinterpret_cast<const float4*>(p + 4);
+  struct Raw {
+    float4 a, b;
+  };
+  __device__ __forceinline__ static void load_raw(const float* p, Raw& r) {
+    r.a = *reinterpret_cast<const float4*>(p);
+    r.b = *reinterpret_cast<const float4*>(p + 4);
+  }
+  __device__ __forceinline__ static void split(const Raw& r, Op8* o) {
+    const float x[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
     split_f32x8(x, o[0], o[1], o[2]);
+  }
+  __device__ __forceinline__ static void load(const float* p, Op8* o) {
+    Raw r;
+    load_raw(p, r);
+    split(r, o);
   }
 };
 
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
     const T* __restrict__ coef_k, const T* __restrict__ coef_v, const int32_t* __restrict__ idx_all,
     int64_t idx_stride, float* __restrict__ part_ml, float* __restrict__ part_o, int n_proc, int nsplit,
     int hq, int hkv, int nb, int rank, int R, int s_sink, int64_t L, int64_t cap, int bases_shared,
-    float theta, Lens lens) {
+    double rope_ratio, Lens lens) {
   constexpr int NP = Parts<T>::n;
   constexpr int NWAVE = DH / 32;          // waves per workgroup
   constexpr int HALF_MB = DH / 32;        // pair offset in 16-dim blocks
@@ -190,14 +191,13 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
   };
   // ---- rotated query for this lane's 8 dims -------------------------------------
   const int64_t pos_q = s_sink + L - 1;
-  double rf[4];
+  uint64_t rf[4];
   float qr[G][8];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) rf[v] = rope_rev_freq(theta, 16 * w + 4 * kg + v, DH);
+  rope_freqs_fixed(rope_ratio, 16 * w + 4 * kg, rf);
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     float c, sn;
-    rope_cs(pos_q, rf[v], c, sn);
+    rope_cs_fixed(pos_q, rf[v], c, sn);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const float xl = qx[g][v], xh = qx[g][4 + v];
@@ -222,29 +222,32 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
     return x < 0 ? 0 : (int64_t)x;
   };
   auto row_off = [&](int64_t tok) -> int64_t { return (tok >> 4) * 16 * (int64_t)R + (tok & 15) * 32 + kg * 8; };
-  auto issue = [&](const T* base, int64_t tok, Op8 (&dst)[RBH][NP]) {
+  typedef typename Parts<T>::Raw Raw;
+  auto issue = [&](const T* base, int64_t tok, Raw (&dst)[RBH]) {
     const int64_t co = row_off(tok);
 #pragma unroll
-    for (int kb = 0; kb < RBH; ++kb) Parts<T>::load(base + co + (int64_t)(kb0 + kb) * 512, dst[kb]);
+    for (int kb = 0; kb < RBH; ++kb) Parts<T>::load_raw(base + co + (int64_t)(kb0 + kb) * 512, dst[kb]);
   };
 
   // one tile's reconstruction, RoPE, logits and online softmax from gathered
   // coefficient operands bk / bv (this lane: token slot, k-group kg)
-  auto compute_tile = [&](int tile, const Op8 (&bk)[RBH][NP], const Op8 (&bv)[RBH][NP]) {
+  auto compute_tile = [&](int tile, const Raw (&bk)[RBH], const Raw (&bv)[RBH]) {
     const bool valid = sidx[(tile - tile0) * 16 + slot] >= 0;
     const int64_t tok = tok_of(tile);
     floatx4 dk[2];
+    dk[0] = dk[1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int hm = 0; hm < 2; ++hm) {
-      dk[hm] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb < RBH; ++kb) {
+      Op8 c[NP];
+      Parts<T>::split(bk[kb], c);
 #pragma unroll
-      for (int kb = 0; kb < RBH; ++kb) {
+      for (int hm = 0; hm < 2; ++hm) {
         if constexpr (KB_LDS) {
           Op8 a0;
           a0.u = *reinterpret_cast<const uint4*>(akop(hm, kb));
-          dk[hm] = mfma16x16x32(a0, bk[kb][0], dk[hm]);
+          dk[hm] = mfma16x16x32(a0, c[0], dk[hm]);
         } else {
-          dk[hm] = mfma_parts<NP, NP>(akop(hm, kb), bk[kb], dk[hm]);
+          dk[hm] = mfma_parts<NP, NP>(akop(hm, kb), c, dk[hm]);
         }
       }
     }
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       float c, sn;
-      rope_cs(s_sink + tok, rf[v], c, sn);
+      rope_cs_fixed(s_sink + tok, rf[v], c, sn);
       const float xl = dk[0][v], xh = dk[1][v];
       kr[v] = xl * c - xh * sn;
       kr[4 + v] = xh * c + xl * sn;
@@ -275,11 +278,13 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
       for (int g = 0; g < G; ++g) xlog[buf][w][g][slot] = part[g];
     }
     floatx4 dv[2];
+    dv[0] = dv[1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int hm = 0; hm < 2; ++hm) {
-      dv[hm] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb < RBH; ++kb) {
+      Op8 c[NP];
+      Parts<T>::split(bv[kb], c);
 #pragma unroll
-      for (int kb = 0; kb < RBH; ++kb) dv[hm] = mfma_parts<NP, NP>(av[hm][kb], bv[kb], dv[hm]);
+      for (int hm = 0; hm < 2; ++hm) dv[hm] = mfma_parts<NP, NP>(av[hm][kb], c, dv[hm]);
     }
     lds_barrier();   // logit exchange; gathers in flight stay in flight
     // online softmax with one running maximum per query head shared by the 16
@@ -310,25 +315,26 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
     }
   };
 
-  // gathers into registers, the next tile's issued before this tile's compute
-  // and kept in flight across its LDS-only barrier
-  Op8 bka[RBH][NP], bkb[RBH][NP], bva[RBH][NP], bvb[RBH][NP];
+  // gathers into registers as stored, the next tile's issued before this
+  // tile's compute and kept in flight across its LDS-only barrier; one copy of
+  // the tile's code (two, for two register sets, were 55 KB at fp32 rank 160,
+  // past what the instruction cache holds)
+  Raw bk[RBH], bv[RBH];
   if (tile0 < tile1) {
-    issue(ckb, tok_of(tile0), bka);
-    issue(cvb, tok_of(tile0), bva);
+    issue(ckb, tok_of(tile0), bk);
+    issue(cvb, tok_of(tile0), bv);
   }
-  for (int tile = tile0; tile < tile1; tile += 2) {
-    {
-      const int64_t tn = tok_of(min(tile + 1, tile1 - 1));
-      issue(ckb, tn, bkb);
-      issue(cvb, tn, bvb);
-    }
-    compute_tile(tile, bka, bva);
-    if (tile + 1 < tile1) {
-      const int64_t tn = tok_of(min(tile + 2, tile1 - 1));
-      issue(ckb, tn, bka);
-      issue(cvb, tn, bva);
-      compute_tile(tile + 1, bkb, bvb);
+#pragma unroll 1
+  for (int tile = tile0; tile < tile1; ++tile) {
+    Raw nk[RBH], nv[RBH];
+    const int64_t tn = tok_of(min(tile + 1, tile1 - 1));
+    issue(ckb, tn, nk);
+    issue(cvb, tn, nv);
+    compute_tile(tile, bk, bv);
+#pragma unroll
+    for (int kb = 0; kb < RBH; ++kb) {
+      bk[kb] = nk[kb];
+      bv[kb] = nv[kb];
     }
   }
 
@@ -357,14 +363,6 @@ __global__ __launch_bounds__(DH * 2, (attn_split_occupancy<T, RBH, G>())) void k
       }
     }
   }
-}
-
-// two fp32 values -> packed bf16 (round to nearest even; one v_cvt_pk_bf16_f32)
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  const f32x2_t v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
 // 8 fp32 values -> one bf16 operand (round to nearest even)

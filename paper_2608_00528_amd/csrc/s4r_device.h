@@ -83,18 +83,33 @@ union Op8 {
   uint16_t h[8];
 };
 
-// 8 fp32 values -> three bf16 operands (hi, mid, lo)
+// two fp32 values -> packed bf16 (round to nearest even; one v_cvt_pk_bf16_f32)
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
+  const f32x2_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// 8 fp32 values -> three bf16 operands (hi, mid, lo); the remainders are exact
+// in fp32.  The hardware's packed conversion takes 11 instructions per pair
+// where rounding by integer arithmetic took 26: the fp32 kernels' time is
+// mostly these splits.
 __device__ __forceinline__ void split_f32x8(const float* x, Op8& hi, Op8& mid, Op8& lo) {
+  uint32_t ph[4], pm[4], pl[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    uint32_t h = f32_to_bf16_bits(x[i]);
-    float r1 = x[i] - bf16_bits_to_f32(h);   // exact in fp32
-    uint32_t m = f32_to_bf16_bits(r1);
-    float r2 = r1 - bf16_bits_to_f32(m);     // exact in fp32
-    hi.h[i] = (uint16_t)h;
-    mid.h[i] = (uint16_t)m;
-    lo.h[i] = (uint16_t)f32_to_bf16_bits(r2);
+  for (int i = 0; i < 4; ++i) {
+    ph[i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
+    float r0 = x[2 * i] - __uint_as_float(ph[i] << 16);
+    float r1 = x[2 * i + 1] - __uint_as_float(ph[i] & 0xFFFF0000u);
+    pm[i] = pack_bf16x2(r0, r1);
+    r0 -= __uint_as_float(pm[i] << 16);
+    r1 -= __uint_as_float(pm[i] & 0xFFFF0000u);
+    pl[i] = pack_bf16x2(r0, r1);
   }
+  hi.u = make_uint4(ph[0], ph[1], ph[2], ph[3]);
+  mid.u = make_uint4(pm[0], pm[1], pm[2], pm[3]);
+  lo.u = make_uint4(pl[0], pl[1], pl[2], pl[3]);
 }
 
 // D = A * B + C for 16x16x32 bf16 (gfx950).  Lane l supplies row l%16 of A
