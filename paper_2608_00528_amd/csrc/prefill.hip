@@ -4,25 +4,32 @@
 //
 // k_transpose_bases first writes every basis group transposed, [column][dim],
 // into the workspace.  k_prefill_project: grid (128-row blocks, basis group x
-// {key, value}, sequence), 4 waves; wave w owns 2 tiles of 16 rows.  The
-// product runs on bf16 MFMA 16x16x32 with fp32 accumulation in the MFMA
-// accumulators: A = the prompt rows as loaded (lane: row l % 16, dims
-// 8 (l / 16) .. + 7 of a 32-dim block), B = the transposed basis slice of the
-// block (one 16-byte LDS read per operand), brought into a ring of LDS buffers
-// by 16-byte global->LDS loads two blocks ahead (lane l of a wave load lands
-// at byte 16 l: 16 columns x 32 dims per instruction); the rows of the next
-// block are in flight in registers.  bf16 inputs make every product exact; the
-// fp32 sums are rounded once to bf16.
+// {key, value}, sequence), 4 waves; wave w owns 2 tiles of 16 rows and walks
+// the group's dims 64 at a time.  The product runs on bf16 MFMA 16x16x32 with
+// fp32 accumulation in the MFMA accumulators: A = the transposed basis slice
+// (one 16-byte LDS read per operand), brought into a ring of three LDS buffers
+// by 16-byte global->LDS loads two steps ahead, B = the prompt rows as loaded
+// (lane: row l % 16, dims 8 (l / 16) .. + 7 of a 32-dim block), two steps ahead
+// in registers, so a lane ends with four consecutive columns of one row and
+// stores 8 bytes.  bf16 inputs make every product exact; the fp32 sums are
+// rounded once to bf16.
+//
+// Bound by reading the rows (2 bytes per raw element; 4 x 131072 rows of K and
+// V at Dp = 1024: 2.15 GB).  A whole 128-byte line of every row is requested
+// per step and 64 KB per CU are in flight; with 64 bytes of a row one step
+// ahead, 2-byte stores and two-way conflicts on the slice reads the same grid
+// ran at 3.5 TB/s: 704 -> 547 us (4.5 TB/s) at that shape, rank 160.
+#include <type_traits>
+
 #include "s4r_device.h"
 #include "s4r_internal.h"
 
 namespace s4r {
 
 constexpr int kPfWaves = 4;
-constexpr int kPfTiles = 2;                       // 16-row tiles per wave (two waves per SIMD:
-                                                  // 737 us at the headline shape, 931 with four
-                                                  // tiles at one wave per SIMD, 864 with one tile)
+constexpr int kPfTiles = 2;                       // 16-row tiles per wave
 constexpr int kPfRows = kPfWaves * kPfTiles * 16;  // rows per workgroup
+constexpr int kPfStep = 64;                       // dims per step (Dp / basis_groups is a multiple of 64)
 
 // s_waitcnt vmcnt(N) alone (gfx9 encoding: expcnt and lgkmcnt not waited)
 template <int N>
@@ -32,7 +39,8 @@ __device__ __forceinline__ void pf_wait_vmcnt() {
 }
 
 // bases [B|1][nb][Dg][rank] -> bt [B][2][nb][rank][Dg]: grid (Dg / 32, 2 nb, B),
-// one 32-row x rank block per workgroup through LDS
+// one 32-row x rank block per workgroup through LDS, 16 bytes per access on
+// both sides (element accesses with a division each took 13.6 us)
 __global__ __launch_bounds__(256) void k_transpose_bases(const uint16_t* __restrict__ bases_k,
                                                          const uint16_t* __restrict__ bases_v,
                                                          uint16_t* __restrict__ bt, int Dg, int nb, int rank,
@@ -44,60 +52,93 @@ __global__ __launch_bounds__(256) void k_transpose_bases(const uint16_t* __restr
                         (int64_t)grp * Dg * rank;
   uint16_t* dst = bt + (((int64_t)b * 2 + which) * nb + grp) * (int64_t)rank * Dg;
   __shared__ uint16_t tile[32][256 + 2];
-  for (int i = threadIdx.x; i < 32 * rank; i += blockDim.x) tile[i / rank][i % rank] = src[(int64_t)(d0 + i / rank) * rank + i % rank];
+  // thread: row t / 8, 8-column pieces t % 8, t % 8 + 8, ..
+  const int r = threadIdx.x >> 3;
+  for (int c8 = threadIdx.x & 7; c8 < rank / 8; c8 += 8) {
+    Op8 v;
+    v.u = *reinterpret_cast<const uint4*>(src + (int64_t)(d0 + r) * rank + c8 * 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) tile[r][c8 * 8 + i] = v.h[i];
+  }
   __syncthreads();
-  for (int i = threadIdx.x; i < 32 * rank; i += blockDim.x) {
-    const int c = i / 32, d = i % 32;
-    dst[(int64_t)c * Dg + d0 + d] = tile[d][c];
+  // thread: dims 8 (t % 4) .. + 7 of columns t / 4, t / 4 + 64, ..
+  const int d8 = (threadIdx.x & 3) * 8;
+  for (int c = threadIdx.x >> 2; c < rank; c += 64) {
+    Op8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v.h[i] = tile[d8 + i][c];
+    *reinterpret_cast<uint4*>(dst + (int64_t)c * Dg + d0 + d8) = v.u;
   }
 }
 
 template <int RBH>
-__global__ __launch_bounds__(kPfWaves * 64) void k_prefill_project(
+__global__ __launch_bounds__(kPfWaves * 64, 2) void k_prefill_project(
     const uint16_t* __restrict__ s_k, const uint16_t* __restrict__ s_v, const uint16_t* __restrict__ bt_all,
     uint16_t* __restrict__ coef_k, uint16_t* __restrict__ coef_v, int64_t n_rows, int hkv, int dh, int nb, int R,
     int64_t cap) {
   constexpr int RANK = RBH * 32;
   constexpr int NCB = RANK / 16;                  // 16-column blocks of the group
-  constexpr int NBUF = 3;                         // slice buffers: two blocks ahead
+  constexpr int NSL = 2 * NCB / kPfWaves;         // slice loads per wave and step (= RBH)
+  constexpr int NROW = 2 * kPfTiles;              // row loads per wave and step
   const int blk = blockIdx.x, gz = blockIdx.y, b = blockIdx.z;
   const int grp = gz >> 1, which = gz & 1;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int slot = lane & 15, kq = lane >> 4;
   const int Dp = hkv * dh, Dg = Dp / nb;
-  const int nkb = Dg / 32;
+  const int ns = Dg / kPfStep;
   const uint16_t* S = (which == 0 ? s_k : s_v) + (int64_t)b * n_rows * Dp + (int64_t)grp * Dg;
   const uint16_t* Bt = bt_all + (((int64_t)b * 2 + which) * nb + grp) * (int64_t)RANK * Dg;
   uint16_t* C = (which == 0 ? coef_k : coef_v) + (int64_t)b * cap * R;
 
-  __shared__ __align__(16) uint16_t bt[NBUF][RANK][32];
+  // slice buffers [32-dim half][column][32 dims], the four 16-byte
+  // quarters of a column's row XORed with (column / 2) % 4 so that the operand
+  // reads of eight consecutive columns hit distinct banks
+  // (three arrays: the loads that refill one then never hold up the reads of
+  // another)
+  __shared__ __align__(16) uint16_t bt0[2][RANK][32], bt1[2][RANK][32], bt2[2][RANK][32];
 
-  const int64_t row0 = (int64_t)blk * kPfRows + (w * kPfTiles) * 16;
-  // slice kb: NCB wave loads of 16 columns x 32 dims, shared out over the waves
-  // (lane l: column 16 n + l / 4, dims 8 (l % 4) .. + 7 -> LDS byte 16 l)
+  const int64_t blk0 = (int64_t)blk * kPfRows;
+  // the workgroup's rows as a buffer: rows past the prompt and steps past the
+  // group lie out of its range and read as zero without a memory access, so
+  // the loads need no branch (which would make the compiler wait for them)
+  const int rows_here = (int)min<int64_t>(kPfRows, n_rows - blk0);
+  const uint32_t nbytes = (uint32_t)((rows_here - 1) * Dp + Dg) * 2u;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(S + blk0 * Dp), (short)0, (int)nbytes, 0x00020000);
+  uint32_t roff[kPfTiles];
+#pragma unroll
+  for (int i = 0; i < kPfTiles; ++i) {
+    const int r = (w * kPfTiles + i) * 16 + slot;
+    roff[i] = r < rows_here ? (uint32_t)(r * Dp + kq * 8) * 2u : 0x80000000u;
+  }
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  auto load_rows = [&](int st, Op8 (&a)[kPfTiles][2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kPfTiles; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t o = st < ns ? roff[i] + (uint32_t)(st * kPfStep + h * 32) * 2u : 0x80000000u;
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+        a[i][h].u = make_uint4(v.x, v.y, v.z, v.w);
+      }
+  };
+  // slice st: 2 NCB wave loads of 16 columns x 32 dims shared out over the
+  // waves (lane l: column l / 4, quarter (l % 4) ^ ((l / 8) % 4) -> LDS byte
+  // 16 l); past the last step the last slice again, into a buffer no longer read
   // (a macro, the LDS destination through a plain local pointer: with the
   // array expression passed to the builtin directly the host pass drops the
   // kernel's launch stub)
-#define S4R_PF_ISSUE_SLICE(KB)                                                                           \
-  do {                                                                                                   \
-    _Pragma("unroll") for (int n0 = 0; n0 < NCB; n0 += kPfWaves) {                                       \
-      const int n_ = n0 + w;                                                                             \
-      if (n_ < NCB) {                                                                                    \
-        uint16_t* dst_ = &bt[(KB) % NBUF][16 * n_][0];                                                   \
-        __builtin_amdgcn_global_load_lds(Bt + (int64_t)(16 * n_ + (lane >> 2)) * Dg + (KB) * 32 + (lane & 3) * 8, \
-                                         dst_, 16, 0, 0);                                                \
-      }                                                                                                  \
-    }                                                                                                    \
+#define S4R_PF_ISSUE_SLICE(BT, ST)                                                                             \
+  do {                                                                                                       \
+    const int st_ = min((ST), ns - 1);                                                                       \
+    _Pragma("unroll") for (int u = 0; u < NSL; ++u) {                                                        \
+      const int n_ = u * kPfWaves + w, h_ = n_ & 1, c_ = n_ >> 1;                                            \
+      uint16_t* dst_ = &BT[h_][16 * c_][0];                                                                   \
+      __builtin_amdgcn_global_load_lds(Bt + (int64_t)(16 * c_ + (lane >> 2)) * Dg + st_ * kPfStep + h_ * 32 + \
+                                           (((lane & 3) ^ ((lane >> 3) & 3)) * 8),                           \
+                                       dst_, 16, 0, 0);                                                      \
+    }                                                                                                        \
   } while (0)
-  // this wave's share of a slice's wave loads (n = w, w + 4, ... < NCB)
-  const int my_slice_loads = w < NCB ? (NCB - w + kPfWaves - 1) / kPfWaves : 0;
-  auto load_rows = [&](int kb, Op8 (&a)[kPfTiles]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < kPfTiles; ++i) {
-      const int64_t r = min(row0 + i * 16 + slot, n_rows - 1);
-      a[i].u = *reinterpret_cast<const uint4*>(S + r * Dp + kb * 32 + kq * 8);
-    }
-  };
 
   floatx4 acc[kPfTiles][NCB];
 #pragma unroll
@@ -105,55 +146,76 @@ __global__ __launch_bounds__(kPfWaves * 64) void k_prefill_project(
 #pragma unroll
     for (int n = 0; n < NCB; ++n) acc[i][n] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // issue order per wave: slice 0, rows 0, slice 1, then in iteration kb rows
-  // kb + 1 before slice kb + 2; so at the top of iteration kb only the loads of
-  // slice kb + 1 may still be in flight
-  Op8 a[kPfTiles];
-  S4R_PF_ISSUE_SLICE(0);
-  load_rows(0, a);
-  if (nkb > 1) S4R_PF_ISSUE_SLICE(1);
-  for (int kb = 0; kb < nkb; ++kb) {
-    // rows kb and this wave's part of slice kb have landed; then every wave's
-    if (kb + 1 < nkb) {
-      switch (my_slice_loads) {
-        case 0: pf_wait_vmcnt<0>(); break;
-        case 1: pf_wait_vmcnt<1>(); break;
-        case 2: pf_wait_vmcnt<2>(); break;
-        default: pf_wait_vmcnt<3>(); break;
-      }
-    } else {
+  // issue order per wave: slice 0, rows 0, slice 1, rows 1, then in step st
+  // rows st + 2 and slice st + 2: at the top of a step only the next step's
+  // loads may still be in flight
+  Op8 a0[kPfTiles][2], a1[kPfTiles][2], a2[kPfTiles][2];
+  S4R_PF_ISSUE_SLICE(bt0, 0);
+  load_rows(0, a0);
+  S4R_PF_ISSUE_SLICE(bt1, 1);
+  load_rows(1, a1);
+  const int koff = (kq ^ ((slot >> 1) & 3)) * 8;
+  auto step = [&](auto buf, auto last, int st, const Op8 (&a)[kPfTiles][2], Op8 (&next)[kPfTiles][2])
+                  __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf)::value;      // st % 3
+    constexpr bool LAST = decltype(last)::value;   // one of the last steps: nothing more to request
+    if constexpr (LAST)
       pf_wait_vmcnt<0>();
+    else
+      pf_wait_vmcnt<NROW + NSL>();
+    lds_barrier();                                 // every wave's part of slice st, and slice st - 1 read
+    if constexpr (!LAST) {
+      load_rows(st + 2, next);
+      if constexpr (BUF == 0)
+        S4R_PF_ISSUE_SLICE(bt2, st + 2);
+      else if constexpr (BUF == 1)
+        S4R_PF_ISSUE_SLICE(bt0, st + 2);
+      else
+        S4R_PF_ISSUE_SLICE(bt1, st + 2);
+      __builtin_amdgcn_sched_barrier(0);           // the requests go out before the products
     }
-    __syncthreads();
-    const bool more = kb + 1 < nkb;
-    Op8 an[kPfTiles];
-    if (more) load_rows(kb + 1, an);
-    if (kb + 2 < nkb) S4R_PF_ISSUE_SLICE(kb + 2);  // its buffer was last read before this barrier
 #pragma unroll
-    for (int n = 0; n < NCB; ++n) {
-      Op8 bop;
-      bop.u = *reinterpret_cast<const uint4*>(&bt[kb % NBUF][n * 16 + slot][kq * 8]);
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int i = 0; i < kPfTiles; ++i) acc[i][n] = mfma16x16x32(a[i], bop, acc[i][n]);
-    }
-    if (more) {
+      for (int n = 0; n < NCB; ++n) {
+        Op8 bop;
+        bop.u = *reinterpret_cast<const uint4*>(BUF == 0   ? &bt0[h][n * 16 + slot][koff]
+                                                : BUF == 1 ? &bt1[h][n * 16 + slot][koff]
+                                                           : &bt2[h][n * 16 + slot][koff]);
 #pragma unroll
-      for (int i = 0; i < kPfTiles; ++i) a[i] = an[i];
-    }
+        for (int i = 0; i < kPfTiles; ++i) acc[i][n] = mfma16x16x32(bop, a[i][h], acc[i][n]);
+      }
+  };
+  // three steps per iteration without a branch between them (at a branch the
+  // compiler waits for every load), the last one or two after the loop
+  constexpr std::integral_constant<int, 0> k0{};
+  constexpr std::integral_constant<int, 1> k1{};
+  constexpr std::integral_constant<int, 2> k2{};
+  int st = 0;
+  for (; st + 3 <= ns; st += 3) {
+    step(k0, std::false_type(), st, a0, a2);
+    step(k1, std::false_type(), st + 1, a1, a0);
+    step(k2, std::false_type(), st + 2, a2, a1);
   }
+  if (st < ns) step(k0, std::true_type(), st, a0, a2);
+  if (st + 1 < ns) step(k1, std::true_type(), st + 1, a1, a0);
 #undef S4R_PF_ISSUE_SLICE
-  // D layout: lane (column slot, row group kq) holds rows 4 kq + v of the tile
+  pf_wait_vmcnt<0>();                              // no load into LDS outlives the workgroup
+  // D layout: lane (row slot, column group kq) holds columns 4 kq + v of block n
   const int c0 = grp * RANK;
 #pragma unroll
-  for (int i = 0; i < kPfTiles; ++i)
+  for (int i = 0; i < kPfTiles; ++i) {
+    const int64_t r = blk0 + (w * kPfTiles + i) * 16 + slot;
+    if (r < n_rows) {
+      uint16_t* cp = C + (r >> 4) * (int64_t)(kTileTok * R) + (r & 15) * kBlkCol;
 #pragma unroll
-    for (int n = 0; n < NCB; ++n)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t r = row0 + i * 16 + 4 * kq + v;
-        const int c = c0 + n * 16 + slot;
-        if (r < n_rows) C[tiled_offset(r, c, R)] = (uint16_t)f32_to_bf16_bits(acc[i][n][v]);
+      for (int n = 0; n < NCB; ++n) {
+        const int c = c0 + n * 16 + 4 * kq;
+        *reinterpret_cast<uint2*>(cp + (c >> 5) * (kTileTok * kBlkCol) + (c & 31)) =
+            make_uint2(pack_bf16x2(acc[i][n][0], acc[i][n][1]), pack_bf16x2(acc[i][n][2], acc[i][n][3]));
       }
+    }
+  }
 }
 
 template <int RBH>
