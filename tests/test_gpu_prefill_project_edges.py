@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 def test_projection_edges(hkv, dh, nb, rank, n, B):
     rng = np.random.default_rng(n + rank)
     Dp = hkv * dh
-    cap = 4096                                                   # (a workspace that holds the transposed bases)
+    cap = 16384                                                  # (a workspace that holds the transposed bases)
     c = s4r.make_config(batch=B, n_q_heads=hkv, n_kv_heads=hkv, head_dim=dh, rank=rank, basis_groups=nb, capacity=cap)
     rs = s4r.rank_stride(rank)
     bf = lambda *s: torch.from_numpy(rng.standard_normal(s)).to(torch.bfloat16)  # noqa: E731
