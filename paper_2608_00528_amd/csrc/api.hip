@@ -269,7 +269,7 @@ Workspace carve_workspace(const Problem& P, void* base) {
   w.wg_stats = (double*)(b + l.off[kWgStats]);
   w.atilde = (float*)(b + l.off[kAtilde]);
   w.hist = (uint32_t*)(b + l.off[kHist]);
-  w.cand = (uint64_t*)(b + l.off[kCand]);
+  w.cand = (uint32_t*)(b + l.off[kCand]);
   w.bitmap = (uint32_t*)(b + l.off[kBitmap]);
   w.idx = (int32_t*)(b + l.off[kIdx]);
   w.part_ml = (float*)(b + l.off[kPartMl]);
@@ -345,9 +345,7 @@ s4r_status s4r_select_topk(const s4r_config* cfg, int64_t L, const float* scores
   S4R_REQ(idx);
   if ((st = check_ws(P, ws, ws_bytes))) return st;
   Workspace w = carve_workspace(P, ws);
-  hipError_t e = launch_hist_only(P, w, L, scores, stream);
-  if (e == hipSuccess) e = launch_select(P, w, L, scores, L, idx, nullptr, stream);
-  return hip_status(e, "s4r_select_topk launch");
+  return hip_status(launch_select(P, w, L, scores, L, idx, nullptr, stream), "s4r_select_topk launch");
 }
 
 s4r_status s4r_reconstruct(const s4r_config* cfg, int64_t L, int32_t m, const int32_t* idx, const void* bases_k,

@@ -86,7 +86,7 @@ struct Workspace {
   double* col_stats;    // [B][GW][2]     global (max, 1 / sum) per query column, when folded by k_fold_stats
   float* atilde;        // [B][cap]       relevance scores
   uint32_t* hist;       // [B][kHistCopies + 1][kHistBins]  selection histograms: copies of the top 11 key bits, next 11 of the boundary bin
-  uint64_t* cand;       // [B][cand_stride]  per-classify-workgroup candidate regions (key << 32 | ~index)
+  uint32_t* cand;       // [B][cand_stride]  per-classify-workgroup candidate regions
   uint32_t* cand_count; // [B][sel_groups_max] candidates found by each classify workgroup
   uint32_t* above_count; // [B][sel_groups_max] positions above the boundary bin per classify workgroup
   uint32_t* sel_info;   // [B][4] boundary bin and the count above it
