@@ -13,10 +13,9 @@
  * ---------------------------------------
  *  - Array pointers are DEVICE pointers, 16-byte aligned, densely packed in
  *    the layouts stated below.  The caller owns all memory; the library does
- *    not allocate device memory on any compute call (the exceptions are named
- *    where they apply: the rocBLAS handle of the basis construction and the
- *    fixed scratch array of s4r_decode_step_noalloc).  Scratch lives in the
- *    caller's workspace, whose
+ *    not allocate device memory on any compute call (the one exception is
+ *    named where it applies: the fixed scratch array of
+ *    s4r_decode_step_noalloc).  Scratch lives in the caller's workspace, whose
  *    size s4r_workspace_size() returns; its initial contents do not matter.
  *  - Every call is asynchronous on the caller's hipStream_t and performs no
  *    host synchronisation.  Calls that share a workspace must not overlap.
@@ -334,18 +333,12 @@ s4r_status s4r_project_queries(const s4r_config* cfg, int64_t n_rows, const void
  * the singular vectors are arbitrary (the decode step depends on B B^T only).
  * s_k / s_v: [B, n_rows, Dp] raw pre-RoPE rows, bf16.  sample_idx_out
  * (optional, device, s4r_prefill_num_samples entries) receives the sample.
- * The Gram matrices are formed in fp64 by this library's kernels; their
- * symmetric eigenproblems run in rocSOLVER (fp64, divide and conquer) within
- * the caller's workspace of s4r_prefill_bases_workspace_size bytes; the first
- * call on a device (this one, or s4r_prefill_bases_workspace_size) creates
- * one rocBLAS handle, kept until the process ends (host threads calling on
- * one device are serialised around it).  Creating the handle is the one
- * place where the library may allocate device memory itself (rocBLAS's own
- * handle state; the solver's workspace is always the caller's).  The call
- * stays asynchronous: the solver's per-matrix convergence flag is consumed
- * on the device, where a matrix that did not converge writes quiet-NaN bases
- * for its (sequence, side, basis group), so the failure reaches the caller
- * through the output instead of passing silently.
+ * The Gram matrices are formed and their leading eigenvectors computed in fp64
+ * (Householder tridiagonalisation, multisection, inverse iteration) by this
+ * library's kernels within the caller's workspace of
+ * s4r_prefill_bases_workspace_size bytes.  A matrix that is not finite (a NaN
+ * or infinity among the sampled rows) gets quiet-NaN bases for its (sequence,
+ * side, basis group), so the failure reaches the caller through the output.
  * bf16 storage, bases_shared = 0, (Dp / basis_groups) % 256 == 0 and at least
  * max(rank, rank_v) sampled rows (otherwise S4R_ERR_UNSUPPORTED /
  * S4R_ERR_BAD_SHAPE).

@@ -121,35 +121,6 @@ struct RawN<float, 4> {
   using type = Raw4f32;
 };
 
-// fp64 move within 16-lane rows (DPP)
-template <int CTRL>
-__device__ __forceinline__ double dpp_move_d(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-// x + y after the gfx950 lane swaps: permlane32_swap exchanges lanes 32..63 of
-// its first operand with lanes 0..31 of its second, permlane16_swap the odd
-// 16-lane rows of the first with the even rows of the second (each dword of
-// the fp64 values the same way).  Afterwards the lower half (even rows) holds
-// the first operand summed over the lane pair, the upper half (odd rows) the
-// second.
-__device__ __forceinline__ double swap32_add(double x, double y) {
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false,
-                                                   false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false,
-                                                   false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-__device__ __forceinline__ double swap16_add(double x, double y) {
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false,
-                                                   false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false,
-                                                   false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-
 // sums of a[0..N) over the 64 lanes of a wave, written to red[wave][0..N):
 // the lane swaps leave row r (lanes 16 r .. 16 r + 15) with values
 // r N / 4 .. + N / 4 - 1 summed over the four rows, DPP sums them within the
@@ -162,10 +133,10 @@ __device__ __forceinline__ void reduce_wave(double (&a)[N], double (*red)[32], i
   for (int j = 0; j < N / 4; ++j) a[j] = swap16_add(a[j], a[j + N / 4]);
 #pragma unroll
   for (int j = 0; j < N / 4; ++j) {
-    a[j] += dpp_move_d<0x128>(a[j]);   // row_ror:8
-    a[j] += dpp_move_d<0x124>(a[j]);   // row_ror:4
-    a[j] += dpp_move_d<0x4E>(a[j]);    // quad_perm [2,3,0,1]
-    a[j] += dpp_move_d<0xB1>(a[j]);    // quad_perm [1,0,3,2]
+    a[j] += dpp_d<0x128>(a[j]);   // row_ror:8
+    a[j] += dpp_d<0x124>(a[j]);   // row_ror:4
+    a[j] += dpp_d<0x4E>(a[j]);    // quad_perm [2,3,0,1]
+    a[j] += dpp_d<0xB1>(a[j]);    // quad_perm [1,0,3,2]
   }
   if ((lane & 15) == 0) {
 #pragma unroll

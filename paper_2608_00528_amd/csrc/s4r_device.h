@@ -219,6 +219,27 @@ __device__ __forceinline__ double wave_sum(double x) {
   return __hiloint2double(bh[0], bl[0]) + __hiloint2double(bh[1], bl[1]);
 }
 
+// x + y after the gfx950 lane swaps: permlane32_swap exchanges lanes 32..63 of
+// its first operand with lanes 0..31 of its second, permlane16_swap the odd
+// 16-lane rows of the first with the even rows of the second (each dword of
+// the fp64 values the same way).  Afterwards the lower half (even rows) holds
+// the first operand summed over the lane pair, the upper half (odd rows) the
+// second.
+__device__ __forceinline__ double swap32_add(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false,
+                                                   false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double swap16_add(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false,
+                                                   false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
 // Workgroup barrier for LDS exchange only: waits for this wave's LDS traffic
 // (lgkmcnt) but not for outstanding global loads (vmcnt), so prefetched
 // global data stays in flight across the barrier.  (__syncthreads() waits for
