@@ -49,21 +49,25 @@ def storage_dtype(cfg):
 
 
 def _ptr(t, name, dtype=None, required=True):
+    """The device address of a tensor argument, as an int (0.3 us a call: a step
+    marshals up to 18 of them beside its launches)."""
     if t is None:
         if required:
             raise ValueError(f"{name} is required")
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle, without the torch.cuda.Stream object around
+    it (0.3 against 3 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _cfgp(cfg):
