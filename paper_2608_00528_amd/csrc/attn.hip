@@ -55,6 +55,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(
   const int n_extra = s_sink + n_win;
   const int half = dh / 2;
   const int64_t pb = ((int64_t)b * hq + h) * kMaxSplit;
+  const float inv_sqrt_d = 1.0f / sqrtf((float)dh);
 
   __shared__ float qr[128];
   __shared__ uint64_t fq[64];
@@ -120,33 +121,24 @@ __global__ __launch_bounds__(256) void k_attn_combine(
       rope_cs_fixed(kpos(e), fq[lane], c, sn);
       part = qr[lane] * (kl * c - kh * sn) + qr[lane + half] * (kh * c + kl * sn);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) part += shfl_xor_f(part, o);
-    if (lane == 0) lg[e] = part / sqrtf((float)dh);
+    part = wave_sum(part);
+    if (lane == 0) lg[e] = part * inv_sqrt_d;
   }
   __syncthreads();
   // ---- (max, sum) of the extra tokens, global maximum, split weights (wave 0) ------------
   if (wave == 0) {
     float mx = -INFINITY;
     for (int e = lane; e < n_extra; e += 64) mx = fmaxf(mx, lg[e]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, shfl_xor_f(mx, o));
+    mx = wave_max(mx);
     float sm = 0.f;
     for (int e = lane; e < n_extra; e += 64) sm += __expf(lg[e] - mx);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sm += shfl_xor_f(sm, o);
-    float M = mx;
-    float ms = (lane < nsplit) ? ml.x : -INFINITY;
-    float m2 = ms;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m2 = fmaxf(m2, shfl_xor_f(m2, o));
-    M = fmaxf(M, m2);
+    sm = wave_sum(sm);
+    const float ms = (lane < nsplit) ? ml.x : -INFINITY;
+    const float M = fmaxf(mx, wave_max(ms));
     const float ae = (n_extra > 0) ? __expf(mx - M) : 0.f;
     const float a = (lane < nsplit && ms != -INFINITY) ? __expf(ms - M) : 0.f;   // empty split: weight 0
     // denominator: the splits' weighted sums (lane = split) plus the extra tokens'
-    float den = (lane < nsplit) ? a * ml.y : 0.f;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) den += shfl_xor_f(den, o);
+    const float den = wave_sum((lane < nsplit) ? a * ml.y : 0.f);
     if (lane == 0) {
       s_me = mx;
       s_ae = ae;
@@ -172,6 +164,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(
   __syncthreads();
   if (t < dh) {
     float num = 0.f;
+#pragma unroll 8
     for (int k = t; k < 1024; k += dh) num += red[k];
     if (n_extra > 0) {
       const float me = s_me;
