@@ -12,9 +12,12 @@ namespace s4r {
 // K1: the coefficient stream
 // ---------------------------------------------------------------------------
 // grid (workgroups per sequence, B) with one block of query columns, else a
-// 1-D grid over (token range, column block); 256 threads = 4 waves.  A wave
-// owns a contiguous range of 16-token tiles; a workgroup scores them against
-// one block of up to 16 query columns (more than one block only when
+// 1-D grid over (token range, column block); 256 threads = 4 waves.  A
+// workgroup owns a contiguous range of 16-token tiles, which its waves take in
+// turn, so it reads one stream of memory (with a range of its own per wave,
+// four streams at distances that are multiples of many channels' interleave,
+// the pass over 4 x 128k tokens took 1.7 us longer of 32.5, over 32 x 32k 1.5
+// of 65); it scores them against one block of up to 16 query columns (more than one block only when
 // G * W_q > 16, the blocks re-reading the tiles from L2 / MALL).  Each 16x32
 // block of C^K is one coalesced 1 KiB wave load that is used directly as the
 // B operand of a 16x16x32 bf16 MFMA (lane l: token l%16, latent columns
@@ -106,8 +109,9 @@ __global__ __launch_bounds__(256, 2) void k_score_stream(
   constexpr int PF = (NP == 1) ? ((NM <= 2 && RB * (A_REG ? 1 + NM / 2 : 1) <= 6) ? 4
                                   : (!A_REG ? (RB <= 5 ? 4 : 2) : (NM * RB <= 16 ? 2 : 1)))
                                 : ((NM <= 2 && RB <= 3) ? 2 : 1);
-  const int tile0 = (xw * kScoreWaves + wave) * tiles_per_wave;
-  const int tile1 = min(tile0 + tiles_per_wave, ntiles);
+  // the workgroup's waves take its tiles in turn
+  const int tile0 = xw * kScoreWaves * tiles_per_wave + wave;
+  const int tile1 = min(xw * kScoreWaves * tiles_per_wave + kScoreWaves * tiles_per_wave, ntiles);
 
   // A operands: query column gi = g * Wq + i (row i of group g's window, oldest
   // first) sits in MFMA m = gi / 4, rows 4 * (gi % 4) + part, as the bf16
@@ -142,7 +146,8 @@ __global__ __launch_bounds__(256, 2) void k_score_stream(
   }
   lds_barrier();                                   // the tile requested above stays in flight
 #pragma unroll
-  for (int p = 1; p < PF; ++p) load_b_tile<T, RB>(cb, min(tile0 + p, tile1 - 1), ntiles, slot, kg, bbuf[p]);
+  for (int p = 1; p < PF; ++p)
+    load_b_tile<T, RB>(cb, min(tile0 + p * kScoreWaves, tile1 - 1), ntiles, slot, kg, bbuf[p]);
   // the A operands stay in registers when they fit, else they are re-read from LDS
   Op8 areg[A_REG ? NM : 1][A_REG ? RB : 1];
   if constexpr (A_REG) {
@@ -178,10 +183,10 @@ __global__ __launch_bounds__(256, 2) void k_score_stream(
     Srun[m] = 0.0;
   }
 
-  for (int tb = tile0; tb < tile1; tb += PF) {
+  for (int tb = tile0; tb < tile1; tb += PF * kScoreWaves) {
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
-      const int tile = tb + p;
+      const int tile = tb + p * kScoreWaves;
       if constexpr (!A_REG) asm volatile("" : "+v"(aoff));
       double acc[NM];
 #pragma unroll
@@ -198,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void k_score_stream(
       }
       // prefetch PF tiles ahead into the buffer just consumed (past the end of
       // this wave's range the load is a harmless re-read of its last tile)
-      load_b_tile<T, RB>(cb, min(tile + PF, tile1 - 1), ntiles, slot, kg, bbuf[p]);
+      load_b_tile<T, RB>(cb, min(tile + PF * kScoreWaves, tile1 - 1), ntiles, slot, kg, bbuf[p]);
       const int tok = tile * 16 + slot;
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
