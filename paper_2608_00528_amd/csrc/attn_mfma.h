@@ -29,26 +29,37 @@
 //   4. the NW partial logits are summed through LDS; lane (t, h) runs the
 //      online softmax of (token t, head h) with one running maximum per head
 //      shared by the 16 token slots;
-//   5. V^ = C^V B^V_j^T (D[token][dim]) of two tiles, rounded once to bf16,
-//      forms the B operand of P V^, with P rounded once to bf16 (moved
-//      between lanes with permutes) as A rows 4 h; the output rows of
-//      head h land in the lanes that own head h's softmax state, which
-//      rescale them when its maximum grows.
+//   5. values stay in latent space: P V^ = (P C^V) B^V_j^T, so the loop forms
+//      P C^V only.  Wave w takes the 16-column blocks w, w + NW, .. of C^V; a
+//      product with the identity turns the tokens of two tiles into the
+//      contraction index (D[token][column], exact in bf16), with P rounded
+//      once to bf16 (moved between lanes with permutes) as A rows 4 h; the
+//      output rows of head h land in the lanes that own head h's softmax state,
+//      which rescale them when its maximum grows;
+//   6. once per split, P C^V (fp32, as three bf16 parts through LDS) times the
+//      value basis.
 // Steps 3-5 are software-pipelined over the tile pairs: after one barrier
-// per pair, a wave runs the softmax and P V^ of pair p (from the partial
+// per pair, a wave runs the softmax and P C^V of pair p (from the partial
 // logits every wave wrote, double-buffered by pair parity) and then K^, RoPE,
-// the partial logits and V^ of pair p + 1, so the two chains' instructions
-// are independent within one basic block (the rescale is branch-free).
+// the partial logits and the turned C^V of pair p + 1, so the two chains'
+// instructions are independent within one basic block (the rescale is
+// branch-free).
+// The loop is bound by VALU and MFMA issue (per tile and wave some 160 VALU
+// instructions, the RoPE phases' at a quarter rate).  Reconstructing V^ in it
+// took 20 MFMAs per tile and wave at rank 160 and the value basis in registers
+// (166 against 144) where the turned C^V takes 6 and P C^V 1.5: 15.4 -> 13.9 us
+// at 4 x 128k (m = 2176), 37 -> 33 at 32 x 32k (m = 1088), 34.5 -> 32 at rank 224
+// and m = 24000.
 //
 // Precision: the logits' operands carry about 16 significant bits each (the
 // rotated query and K~ as hi / lo parts), since a logit error enters the
 // weights through the exponential: with heavy-tailed coefficients logits
 // reach tens, where a bf16 K~ (relative error 2^-9 per element) moved the
-// output by 1.3e-2, most of the 2e-2 bound for bf16 storage.  V^ enters the
-// output linearly, so it is rounded once to bf16 (at most 2^-9 relative per
-// element, a few 1e-3 at the output), and so is P (each weight within 2^-9
-// relative; the normaliser sums the unrounded weights): the largest output
-// error over the parity cases went from 4e-3 to 6e-3; every sum is fp32.
+// output by 1.3e-2, most of the 2e-2 bound for bf16 storage.  P enters the
+// output linearly and is rounded once to bf16 (each weight within 2^-9 relative;
+// the normaliser sums the unrounded weights); the values are not rounded at
+// all, every sum is fp32: 2-norm output errors of 0.6e-3 to 1.2e-3 against 64
+// bits, 0.9e-3 to 1.7e-3 when V^ was rounded to bf16 as well.
 //
 // Each split writes its (max, sum) and unnormalised output per head.
 #pragma once
@@ -114,6 +125,7 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
     int64_t cap,
     int bases_shared, double rope_ratio, Lens lens) {
   constexpr int DH = NW * 32;                      // NMH = ceil(G / 4): 4 heads per MFMA row group
+  constexpr int NCB = (2 * RBV + NW - 1) / NW;     // 16-column blocks of C^V per wave
   static_assert(NW >= 2, "a tile pair is gathered by two waves");
   // ---- work item: KV head j of group (sequence, split); the workgroups of
   // one group share an XCD ------------------------------------------------------------------
@@ -149,6 +161,9 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
   __shared__ __align__(16) uint16_t gkB[2][RBH][512], gvB[2][RBV][512];
   __shared__ int32_t sidx[kTileMax * 16];
   __shared__ float xl[2][2][NW][NMH][4][16];             // partial logits [pair & 1][tile of pair][wave][mh][head][slot]
+  // the split's P C^V as bf16 parts: row 4 head + part, columns padded by 16
+  // bytes (the operand reads of 16 rows hit distinct banks)
+  __shared__ __align__(16) uint16_t olat[NMH][16][RBV * 32 + 8];
 
   // ---- 1. index list, bases and query requested; then the first two pairs' gathers ---------
   int32_t xi[kTileMax * 16 / (NW * 64)];
@@ -169,21 +184,17 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
       return sidx[i];
     }
   };
-  // bases (registers): A operands of K^ (row = dim) and B operands of V^
-  // (column = dim) read the same 16-byte pattern of their basis
+  // key basis (registers): A operands of K^ (row = dim); the value basis is
+  // read at the end
   const int64_t boff = (bases_shared ? 0 : (int64_t)b * Dp * rank) + (int64_t)bgrp * Dg * rank;
   const int64_t boffv = (bases_shared ? 0 : (int64_t)b * Dp * rank_v) + (int64_t)bgrp * Dg * rank_v;
-  Op8 bk[2][RBH], bv[2][RBV];
+  Op8 bk[2][RBH];
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
     const int d = 16 * (w + m * NW) + slot;
 #pragma unroll
     for (int kb = 0; kb < RBH; ++kb)
       bk[m][kb].u = *reinterpret_cast<const uint4*>(bases_k + boff + (int64_t)(row0 + d) * rank + kb * 32 + kg * 8);
-#pragma unroll
-    for (int kb = 0; kb < RBV; ++kb)
-      bv[m][kb].u =
-          *reinterpret_cast<const uint4*>(bases_v + boffv + (int64_t)(row0 + d) * rank_v + kb * 32 + kg * 8);
   }
   // the query dims of this lane's k-group: f_v = 16 w + 4 kg + v and f_v + d_h / 2
   const int fq = 16 * w + 4 * kg;
@@ -248,20 +259,29 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
     }
   }
   float Mrun[NMH], lrun[NMH];
-  floatx4 oacc[NMH][2];
+  floatx4 oacc[NMH][NCB];
 #pragma unroll
   for (int mh = 0; mh < NMH; ++mh) {
     Mrun[mh] = -INFINITY;
     lrun[mh] = 0.f;
-    oacc[mh][0] = floatx4{0.f, 0.f, 0.f, 0.f};
-    oacc[mh][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NCB; ++i) oacc[mh][i] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
+  // this wave's column blocks of C^V: block w + NW i is half w % 2 of 32-column
+  // block w / 2 + NW / 2 i (past the last: a repeat, left out at the end), and
+  // the identity's columns of that half as an MFMA operand
+  int vcol[NCB];
+#pragma unroll
+  for (int i = 0; i < NCB; ++i) vcol[i] = min((w >> 1) + (NW / 2) * i, RBV - 1) * 512 + kq;
+  Op8 eye;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) eye.h[i] = 16 * (w & 1) + slot == 8 * kg + i ? 0x3F80 : 0;
   const float inv_sqrt_d = 1.0f / sqrtf((float)DH);
 
   // ---- 3-5. software-pipelined over tile pairs: the softmax and P V^ of pair p
   // run beside the reconstruction of pair p + 1, with one barrier per pair ------------------
-  // stage: K^, RoPE and the wave's partial logits of pair q (buffer BUF) -> xl[q & 1]; V^ -> dv
-  auto stage_pair = [&](const int q, auto buf, floatx4 (&dv)[2][2], int32_t (&tokv)[2])
+  // stage: K^, RoPE and the wave's partial logits of pair q (buffer BUF) -> xl[q & 1]; C^V turned -> vt
+  auto stage_pair = [&](const int q, auto buf, Op8 (&vt)[NCB], int32_t (&tokv)[2])
                         __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf)::value;
 #pragma unroll
@@ -298,21 +318,24 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
         dl = mfma16x16x32(aq[mh], klo, dl);
         xl[q & 1][u][w][mh][kg][slot] = dl[0] + dl[1];
       }
-      // V^ of this tile: lane (dim, kg) gets tokens 4 kg + v
+    }
+    // C^V of both tiles turned by a product with the identity: lane (column,
+    // kg) gets tokens 4 kg + v, exact
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        dv[u][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NCB; ++i) {
+      floatx4 d[2];
 #pragma unroll
-        for (int kb = 0; kb < RBV; ++kb) {
-          Op8 c;
-          c.u = *reinterpret_cast<const uint4*>(BUF == 0 ? &gvA[u][kb][kq] : &gvB[u][kb][kq]);
-          dv[u][m] = mfma16x16x32(c, bv[m][kb], dv[u][m]);
-        }
+      for (int u = 0; u < 2; ++u) {
+        Op8 c;
+        c.u = *reinterpret_cast<const uint4*>(BUF == 0 ? &gvA[u][0][0] + vcol[i] : &gvB[u][0][0] + vcol[i]);
+        d[u] = mfma16x16x32(c, eye, floatx4{0.f, 0.f, 0.f, 0.f});
       }
+      vt[i].u = make_uint4(pack_bf16x2(d[0][0], d[0][1]), pack_bf16x2(d[0][2], d[0][3]),
+                           pack_bf16x2(d[1][0], d[1][1]), pack_bf16x2(d[1][2], d[1][3]));
     }
   };
-  // finish: online softmax of pair q from every wave's partial logits, then P V^
-  auto finish_pair = [&](const int q, const floatx4 (&dv)[2][2], const int32_t (&tokv)[2])
+  // finish: online softmax of pair q from every wave's partial logits, then P C^V
+  auto finish_pair = [&](const int q, const Op8 (&vt)[NCB], const int32_t (&tokv)[2])
                          __attribute__((always_inline)) {
     float sl[2][NMH];
 #pragma unroll
@@ -334,8 +357,8 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
       const float mnew = fmaxf(Mrun[mh], slot_max16(fmaxf(sl[0][mh], sl[1][mh])));
       const float alpha = (mnew == -INFINITY) ? 1.f : __expf(Mrun[mh] - mnew);   // 0 when the maximum was -inf
       lrun[mh] *= alpha;
-      oacc[mh][0] *= alpha;
-      oacc[mh][1] *= alpha;
+#pragma unroll
+      for (int i = 0; i < NCB; ++i) oacc[mh][i][0] *= alpha;   // (rows 4 h + 1..3 stay zero)
       Mrun[mh] = mnew;
       float pr[2];
 #pragma unroll
@@ -346,18 +369,10 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
       // P of both tiles rounded to bf16, packed (tile 0 low half, tile 1 high half)
       phi[mh] = pack_bf16x2(pr[0], pr[1]);
     }
-    // P V^: A = P (row 4 h, k = tokens 4 kg + v of both tiles; rows 4 h + 1..3
-    // zero), B = V^ rounded to bf16.  Every wave builds its own A operand from
-    // the softmax lanes with lane permutes (lane (row 4 h, k-group c) takes
-    // token 4 c + v, head h from lane (4 c + v) + 16 h), so P never goes
-    // through LDS and needs no barrier
-    Op8 vb16[2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const float x[8] = {dv[0][m][0], dv[0][m][1], dv[0][m][2], dv[0][m][3],
-                          dv[1][m][0], dv[1][m][1], dv[1][m][2], dv[1][m][3]};
-      round_f32x8(x, vb16[m]);
-    }
+    // P C^V: A = P (row 4 h, k = tokens 4 kg + v of both tiles; rows 4 h + 1..3
+    // zero).  Every wave builds its own A operand from the softmax lanes with
+    // lane permutes (lane (row 4 h, k-group c) takes token 4 c + v, head h from
+    // lane (4 c + v) + 16 h), so P never goes through LDS and needs no barrier
     const int hh = slot >> 2, part = slot & 3;
 #pragma unroll
     for (int mh = 0; mh < NMH; ++mh) {
@@ -372,7 +387,7 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
       ap.u = make_uint4((r[0] & 0xFFFFu) | (r[1] << 16), (r[2] & 0xFFFFu) | (r[3] << 16),
                         (r[0] >> 16) | (r[1] & 0xFFFF0000u), (r[2] >> 16) | (r[3] & 0xFFFF0000u));
 #pragma unroll
-      for (int m = 0; m < 2; ++m) oacc[mh][m] = mfma16x16x32(ap, vb16[m], oacc[mh][m]);
+      for (int i = 0; i < NCB; ++i) oacc[mh][i] = mfma16x16x32(ap, vt[i], oacc[mh][i]);
     }
   };
   // refill the buffer of pair q - 2 (free once every wave staged it) with pair q
@@ -393,22 +408,20 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
   };
   // iteration p: pair p + 1's rows have landed (the only gathers in flight),
   // every wave has staged pair p (xl[p & 1] complete, buffer of pair p free)
-  auto iterate = [&](const int p, auto buf, floatx4 (&dv)[2][2], int32_t (&tokv)[2])
+  auto iterate = [&](const int p, auto buf, Op8 (&vt)[NCB], int32_t (&tokv)[2])
                      __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf)::value;    // buffer of pair p
     wait_vmcnt<0>();
     lds_barrier();
     refill(p + 2, buf);
-    floatx4 dvn[2][2];
+    Op8 vn[NCB];
     int32_t tokn[2];
-    finish_pair(p, dv, tokv);
-    stage_pair(p + 1, std::integral_constant<int, 1 - BUF>(), dvn, tokn);
+    finish_pair(p, vt, tokv);
+    stage_pair(p + 1, std::integral_constant<int, 1 - BUF>(), vn, tokn);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      tokv[u] = tokn[u];
+    for (int u = 0; u < 2; ++u) tokv[u] = tokn[u];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) dv[u][m] = dvn[u][m];
-    }
+    for (int i = 0; i < NCB; ++i) vt[i] = vn[i];
   };
   // pair 0's rows (pair 1's gathers may stay in flight), then stage it
   if ((2 % NW) == w || (3 % NW) == w)
@@ -416,20 +429,64 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
   else
     wait_vmcnt<0>();
   lds_barrier();
-  floatx4 dvc[2][2];
+  Op8 vtc[NCB];
   int32_t tokc[2];
-  stage_pair(0, std::integral_constant<int, 0>(), dvc, tokc);
+  stage_pair(0, std::integral_constant<int, 0>(), vtc, tokc);
   int p = 0;
   for (; p + 2 < npair; p += 2) {
-    iterate(p, std::integral_constant<int, 0>(), dvc, tokc);
-    iterate(p + 1, std::integral_constant<int, 1>(), dvc, tokc);
+    iterate(p, std::integral_constant<int, 0>(), vtc, tokc);
+    iterate(p + 1, std::integral_constant<int, 1>(), vtc, tokc);
   }
   if (p + 1 < npair) {
-    iterate(p, std::integral_constant<int, 0>(), dvc, tokc);
+    iterate(p, std::integral_constant<int, 0>(), vtc, tokc);
     ++p;
   }
+  // the value basis as B operands (column = dim), overlapping the last pair's softmax
+  Op8 bv[2][RBV];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const int d = 16 * (w + m * NW) + slot;
+#pragma unroll
+    for (int kb = 0; kb < RBV; ++kb)
+      bv[m][kb].u =
+          *reinterpret_cast<const uint4*>(bases_v + boffv + (int64_t)(row0 + d) * rank_v + kb * 32 + kg * 8);
+  }
   lds_barrier();                                   // xl of the last pair complete
-  finish_pair(p, dvc, tokc);
+  finish_pair(p, vtc, tokc);
+
+  // ---- B^V applied to the split's P C^V: its fp32 values as three bf16 parts in
+  // rows 4 head + part (row 4 head + 3 is never used), so lane (dim, kg) gets the
+  // three partial products of head kg ----------------------------------------------------
+#pragma unroll
+  for (int mh = 0; mh < NMH; ++mh)
+#pragma unroll
+    for (int i = 0; i < NCB; ++i) {
+      const int cb = w + NW * i;
+      if (cb < 2 * RBV) {
+        const float x = oacc[mh][i][0];
+        const uint32_t hi = f32_to_bf16_bits(x);
+        const float r1 = x - bf16_bits_to_f32(hi);
+        const uint32_t mid = f32_to_bf16_bits(r1);
+        const float r2 = r1 - bf16_bits_to_f32(mid);
+        uint16_t* o = &olat[mh][4 * kg][cb * 16 + slot];
+        o[0] = (uint16_t)hi;
+        o[RBV * 32 + 8] = (uint16_t)mid;
+        o[2 * (RBV * 32 + 8)] = (uint16_t)f32_to_bf16_bits(r2);
+      }
+    }
+  lds_barrier();
+  floatx4 od[NMH][2];
+#pragma unroll
+  for (int mh = 0; mh < NMH; ++mh) {
+    od[mh][0] = od[mh][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < RBV; ++kb) {
+      Op8 a;
+      a.u = *reinterpret_cast<const uint4*>(&olat[mh][slot][kb * 32 + kg * 8]);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) od[mh][m] = mfma16x16x32(a, bv[m][kb], od[mh][m]);
+    }
+  }
   wait_vmcnt<0>();                                 // no gather left in flight (a second pair that
                                                    // was never used when there is one pair only)
 
@@ -446,7 +503,8 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
         part_ml[pb * 2 + 1] = lsum;
       }
 #pragma unroll
-      for (int m = 0; m < 2; ++m) part_o[pb * DH + 16 * (w + m * NW) + slot] = oacc[mh][m][0] + oacc[mh][m][1];
+      for (int m = 0; m < 2; ++m)
+        part_o[pb * DH + 16 * (w + m * NW) + slot] = od[mh][m][0] + (od[mh][m][1] + od[mh][m][2]);
     }
   }
 }
