@@ -24,7 +24,7 @@
 //   k_tri_back      Q applied to them.
 // The chain of columns bounds it: Dg dependent steps, each a launch, a read of
 // what the step before wrote and two block-wide sums (about 5 us).  One 32k
-// prompt at Dg = 1024, rank 160 (two matrices): 7.9 ms against 23.5 ms in
+// prompt at Dg = 1024, rank 160 (two matrices): 7.3 ms against 23.5 ms in
 // a library solver that computes all eigenvectors by divide and conquer in
 // some 4500 launches.
 #include <algorithm>
@@ -142,29 +142,42 @@ __global__ __launch_bounds__(256) void k_gram(const uint16_t* __restrict__ s_k, 
     for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
   const int i0 = ti * kGramTile, j0 = tj * kGramTile;
   // the next round's sample values are requested before this round's MFMAs
-  // run and written to LDS after them (8 per thread and column range)
+  // run and written to LDS after them (8 per thread and column range: sample
+  // wave + 4 k, column lane); the round after's positions are read with them,
+  // so a round waits for one memory latency and not for two in a row (955 ->
+  // 618 us for two matrices of 6553 samples at Dg = 1024)
   constexpr int kPer = kGramChunk * kGramTile / 256;
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
   uint16_t ra[kPer], rb[kPer];
-  double rw[kPer];
+  double rw[kPer], nw[kPer];
+  int32_t nid[kPer];
+  auto positions = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int s = min(s0 + wv + 4 * k, n_s - 1);
+      nid[k] = idx[s];
+      nw[k] = inv_m[s];
+    }
+  };
   auto fetch = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int e = t + k * 256, r = e / kGramTile, col = e % kGramTile;
-      const int s = min(s0 + r, n_s - 1);
-      const uint16_t* row = base + (int64_t)idx[s] * Dp;
-      ra[k] = row[i0 + col];
-      rb[k] = row[j0 + col];
-      rw[k] = (s0 + r < n_s) ? inv_m[s] : 0.0;
+      const uint16_t* row = base + (int64_t)nid[k] * Dp + lane;
+      ra[k] = row[i0];
+      rb[k] = row[j0];
+      rw[k] = s0 + wv + 4 * k < n_s ? nw[k] : 0.0;
     }
+    positions(s0 + kGramChunk);
   };
   auto stage = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int e = t + k * 256, r = e / kGramTile, col = e % kGramTile;
+      const int r = wv + 4 * k, col = lane;
       xa[r][col] = (double)bf16_bits_to_f32(ra[k]) * rw[k];
       xb[r][col] = (double)bf16_bits_to_f32(rb[k]) * rw[k];
     }
   };
+  positions(0);
   fetch(0);
   stage();
   __syncthreads();
