@@ -135,7 +135,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t elem_size(const Problem& P) { return P.dtype == S4R_BF16 ? 2 : 4; }
 
 enum Region {
-  kQimg, kQcoef, kE, kRunM, kWgStats, kAtilde, kHist, kCand, kBitmap, kIdx, kPartMl, kPartO, kAttnLogits,
+  kQimg, kQcoef, kE, kRunM, kWgStats, kAtilde, kHist, kCand, kBitmap, kIdx, kPartMl, kPartO, kReserved,
   kCandCount, kAboveCount, kSelInfo, kColStats, kRegions
 };
 struct Layout {
@@ -158,7 +158,9 @@ Layout layout(const Problem& P) {
   sizes[kIdx] = B * P.m_max * 4;
   sizes[kPartMl] = B * P.hq * kMaxSplit * 2 * 4;
   sizes[kPartO] = B * P.hq * kMaxSplit * P.dh * 4;
-  sizes[kAttnLogits] = B * P.hq * (P.s + P.m_max) * 4;
+  // no kernel uses it; it keeps the workspace at the size that callers have
+  // allocated and that the entry points' size checks compare with
+  sizes[kReserved] = B * P.hq * (P.s + P.m_max) * 4;
   sizes[kCandCount] = B * sel_groups_max(P) * 4;
   sizes[kAboveCount] = B * sel_groups_max(P) * 4;
   sizes[kSelInfo] = B * 4 * 4;
@@ -274,7 +276,6 @@ Workspace carve_workspace(const Problem& P, void* base) {
   w.idx = (int32_t*)(b + l.off[kIdx]);
   w.part_ml = (float*)(b + l.off[kPartMl]);
   w.part_o = (float*)(b + l.off[kPartO]);
-  w.attn_logits = (float*)(b + l.off[kAttnLogits]);
   w.cand_count = (uint32_t*)(b + l.off[kCandCount]);
   w.above_count = (uint32_t*)(b + l.off[kAboveCount]);
   w.sel_info = (uint32_t*)(b + l.off[kSelInfo]);

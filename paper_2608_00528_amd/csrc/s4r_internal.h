@@ -94,7 +94,6 @@ struct Workspace {
   int32_t* idx;         // [B][m_max]
   float* part_ml;       // [B][hq][kMaxSplit][2]   split partial (max, sum)
   float* part_o;        // [B][hq][kMaxSplit][dh]  split partial outputs
-  float* attn_logits;   // [B][hq][s + m_max]      explicit-attention scratch
   size_t total;
 };
 
