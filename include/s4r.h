@@ -336,9 +336,12 @@ s4r_status s4r_project_queries(const s4r_config* cfg, int64_t n_rows, const void
  * The Gram matrices are formed and their leading eigenvectors computed in fp64
  * (Householder tridiagonalisation, multisection, inverse iteration) by this
  * library's kernels within the caller's workspace of
- * s4r_prefill_bases_workspace_size bytes.  A matrix that is not finite (a NaN
- * or infinity among the sampled rows) gets quiet-NaN bases for its (sequence,
- * side, basis group), so the failure reaches the caller through the output.
+ * s4r_prefill_bases_workspace_size bytes.  Within equal eigenvalues any
+ * orthonormal vectors of their space may come out (the same on every call).  A
+ * matrix that is not finite (a NaN or infinity among the sampled rows), or
+ * whose vectors cannot be made orthonormal from any of the solver's starts,
+ * gets quiet-NaN bases for its (sequence, side, basis group), so the failure
+ * reaches the caller through the output.
  * bf16 storage, bases_shared = 0, (Dp / basis_groups) % 256 == 0 and at least
  * max(rank, rank_v) sampled rows (otherwise S4R_ERR_UNSUPPORTED /
  * S4R_ERR_BAD_SHAPE).

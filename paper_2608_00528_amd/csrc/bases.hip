@@ -16,11 +16,12 @@
 //                   column;
 //   k_tri_values    the wanted eigenvalues of T by multisection on the Sturm
 //                   count, one wave each;
-//   k_tri_vectors   their eigenvectors by inverse iteration (LU of T - lambda
+//   k_tri_vectors   their eigenvectors by inverse iteration (LU of T - shift
 //                   with partial pivoting), one lane each;
 //   k_z_gram, k_z_chol, k_z_solve   their orthonormalisation by a Cholesky
 //                   factor of Z^T Z (inverse iteration leaves vectors of close
-//                   eigenvalues slightly oblique);
+//                   eigenvalues oblique), repeated where the first pass finds
+//                   them far from orthogonal;
 //   k_tri_back      Q applied to them.
 // The chain of columns bounds it: Dg dependent steps, each a launch, a read of
 // what the step before wrote and two block-wide sums (about 5 us).  One 32k
@@ -472,41 +473,72 @@ __global__ __launch_bounds__(256) void k_tri_values(const double* __restrict__ d
 // ---- eigenvectors of T ------------------------------------------------------------------------
 // Inverse iteration, one lane per eigenvalue: EV = 2048 / n of them per
 // workgroup (one wave; T and the factors of its lanes in LDS, so the serial
-// sweeps over n run at LDS latency).  LU of T / norm - lambda with partial
-// pivoting, a random start, three solves (the first by U alone).
+// sweeps over n run at LDS latency).  LU of T / norm - (lambda + kShift) with
+// partial pivoting, a start vector of its own, two solves (the first by U alone).
+//
+// Eigenvalues may coincide to rounding: repeated or orthogonal rows, equal
+// blocks, the zeros of a prompt with few distinct rows.  At the eigenvalue
+// itself a solve would magnify most whichever member of the cluster rounding
+// puts nearest, the same one in every lane.  kShift keeps all of them at about
+// the same distance, some 500 times the rounding of T's norm, so a cluster's
+// vectors are its starts projected on its space and stay independent; two
+// solves leave a neighbour at a gap g (1 = the norm) with (kShift / g)^2 of
+// its start: 1e-14 at 1e-6, and a mixture below 1e-12 costs no more energy
+// than the gap.  In clusters, block and projection matrices and graded spectra
+// of 256 to 1024 columns the smallest pivot of the Cholesky factor is 1e-4 at
+// the median and 1e-12 at worst with two solves, lost altogether in one
+// of a hundred with three (and at the eigenvalue itself in most).
+constexpr double kShift = 1.1368683772161603e-13;   // 2^-43
+
+// orthonormalisation rounds per matrix, what each leaves in
+// state[mat] = 4 round + code, and the pivots that decide: 1 is a unit vector
+// orthogonal to those before it, and the factor's error grows with its inverse
+constexpr int kOrthoRounds = 3;
+enum OrthoCode { kOrthoDone = 0, kOrthoAgain = 1, kOrthoLost = 2 };   // Lost: other start vectors
+constexpr double kPivAgain = 1e-3, kPivLost = 1e-12;
+// whether matrix mat takes part in a round, given the code the round before left
+__device__ __forceinline__ bool ortho_active(const int32_t* info, const int32_t* state, int64_t mat, int round,
+                                             int code) {
+  return info[mat] == 0 && (round == 0 || (state[mat] & 3) >= code);
+}
+
+// component i of start vector q of a round, in [-1, 1): the index times the
+// bits of the golden ratio plus the vector's times those of sqrt(2), folded
+// and multiplied again so that different q share no pattern
+__device__ __forceinline__ double start_component(int i, int q, int round) {
+  constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull, kRoot2 = 0x6A09E667F3BCC909ull;
+  uint64_t h = (uint64_t)(i + 1) * kGolden + (uint64_t)(q + 1 + 4096 * round) * kRoot2;
+  h = (h ^ (h >> 32)) * kGolden;
+  h = (h ^ (h >> 29)) * kRoot2;
+  return (double)(int64_t)h * (1.0 / 9223372036854775808.0);
+}
+
 __global__ __launch_bounds__(64) void k_tri_vectors(const double* __restrict__ d_all, const double* __restrict__ e_all,
                                                     const double* __restrict__ lam, const double* __restrict__ norm,
-                                                    const int32_t* __restrict__ info, double* __restrict__ Z, int n,
-                                                    int rk, int rv, int rmax, int ev) {
+                                                    const int32_t* __restrict__ info,
+                                                    const int32_t* __restrict__ state, double* __restrict__ Z, int n,
+                                                    int rk, int rv, int rmax, int ev, int round) {
   const int64_t mat = blockIdx.y;
   const int lane = threadIdx.x;
   const int r = (mat & 1) == 0 ? rk : rv;
+  if (!ortho_active(info, state, mat, round, kOrthoLost)) return;
   __shared__ double ds[2048 + 16], es[2048 + 16];
   __shared__ double li[2048], pi[2048], u1[2048], u2[2048], xs[2048];   // [k][ev]
   __shared__ uint8_t sw[2048];
   const int q0 = blockIdx.x * ev;
-  if (q0 >= r || info[mat]) return;
+  if (q0 >= r) return;
   const double inv = 1.0 / norm[mat];
   for (int i = lane; i < n; i += 64) {
     ds[i] = d_all[mat * n + i] * inv;
     es[i] = e_all[mat * n + i] * inv;
   }
   if (lane < 16) ds[n + lane] = es[n + lane] = 0.0;
-  // start vectors: a hash of (component, q) in [-1, 1)
-  for (int i = lane; i < n * ev; i += 64) {
-    uint32_t h = (uint32_t)(i / ev) * 2654435761u ^ ((uint32_t)(q0 + i % ev) + 1u) * 2246822519u;
-    h ^= h >> 15;
-    h *= 2246822519u;
-    h ^= h >> 13;
-    h *= 3266489917u;
-    h ^= h >> 16;
-    xs[i] = (double)(int32_t)h * (1.0 / 2147483648.0);
-  }
+  for (int i = lane; i < n * ev; i += 64) xs[i] = start_component(i / ev, q0 + i % ev, round);
   lds_barrier();
   const int q = min(q0 + lane, r - 1);
   if (lane < ev) {
     constexpr double kTiny = 2.2e-16;              // smallest pivot, for a norm of 1
-    const double x = lam[mat * rmax + q];
+    const double x = lam[mat * rmax + q] + kShift;
     auto at = [&](int k) { return k * ev + lane; };
     double b = ds[0] - x, c = es[0];
     for (int k0 = 0; k0 < n; k0 += 8) {             // (n is a multiple of 256; T has zeros after its end)
@@ -538,7 +570,7 @@ __global__ __launch_bounds__(64) void k_tri_vectors(const double* __restrict__ d
       }
     }
     double sc = 1.0;                               // applied when a sweep reads x
-    for (int it = 0; it < 3; ++it) {
+    for (int it = 0; it < 2; ++it) {
       if (it > 0) {                                // x = L^-1 P x
         double cur = xs[at(0)] * sc;
         for (int k0 = 0; k0 + 1 < n; k0 += 8) {
@@ -604,10 +636,12 @@ __global__ __launch_bounds__(64) void k_tri_vectors(const double* __restrict__ d
 // ---- orthonormalisation -----------------------------------------------------------------------
 // G = Z Z^T over the r vectors (rows of Z, length n), lower tiles of 16 x 16:
 // grid (tiles, matrices), thread (a, b) one element
-__global__ __launch_bounds__(256) void k_z_gram(const double* __restrict__ Z, double* __restrict__ G, int n, int rk,
-                                                int rv, int rmax) {
+__global__ __launch_bounds__(256) void k_z_gram(const double* __restrict__ Z, double* __restrict__ G,
+                                                const int32_t* __restrict__ info, const int32_t* __restrict__ state,
+                                                int n, int rk, int rv, int rmax, int round) {
   const int64_t mat = blockIdx.y;
   const int r = (mat & 1) == 0 ? rk : rv;
+  if (!ortho_active(info, state, mat, round, kOrthoAgain)) return;
   int ta = 0, rem = blockIdx.x;
   while (rem > ta) {
     rem -= ta + 1;
@@ -636,17 +670,22 @@ __global__ __launch_bounds__(256) void k_z_gram(const double* __restrict__ Z, do
 // Cholesky factor of G, one workgroup per matrix (four quarters of the inner
 // sum per row): L row-major over G's lower triangle in place, its diagonal as
 // the reciprocal; the columns already found are read from LDS (column j from
-// its diagonal down) up to kCholLds vectors, else from LT in memory
+// its diagonal down) up to kCholLds vectors, else from LT in memory.  Its
+// smallest pivot decides whether the matrix needs another round (a NaN among
+// the vectors counts as lost)
 constexpr int kCholLds = 180;
 template <bool LDS>
-__global__ __launch_bounds__(1024) void k_z_chol(double* __restrict__ G, double* __restrict__ LT, int rk, int rv,
-                                                 int rmax) {
+__global__ __launch_bounds__(1024) void k_z_chol(double* __restrict__ G, double* __restrict__ LT,
+                                                 const int32_t* __restrict__ info, int32_t* __restrict__ state, int rk,
+                                                 int rv, int rmax, int round) {
   const int64_t mat = blockIdx.x;
   const int r = (mat & 1) == 0 ? rk : rv;
+  if (!ortho_active(info, state, mat, round, kOrthoAgain)) return;
   const int i = threadIdx.x & 255, qr = threadIdx.x >> 8;
   double* Gm = G + mat * rmax * rmax;
   double* Lm = LT + mat * rmax * rmax;
   __shared__ double red[4][256], s_piv;
+  int code = kOrthoDone;                           // uniform: every thread reads every pivot
   __shared__ double lc[LDS ? kCholLds * (kCholLds + 1) / 2 : 1];
   auto col = [&](int j) { return j * r - j * (j - 1) / 2 - j; };   // L[i][j] at lc[col(j) + i]
   for (int k = 0; k < r; ++k) {
@@ -664,11 +703,17 @@ __global__ __launch_bounds__(1024) void k_z_chol(double* __restrict__ G, double*
     const double gik = qr == 0 && i >= k && i < r ? Gm[(int64_t)i * rmax + k] : 0.0;
     __syncthreads();
     const double s = gik - ((red[0][i] + red[1][i]) + (red[2][i] + red[3][i]));
-    if (qr == 0 && i == k) s_piv = 1.0 / sqrt(fmax(s, 1e-30));
+    if (qr == 0 && i == k) s_piv = s;
     __syncthreads();
+    const double piv = s_piv;
+    if (!(piv > kPivLost)) {
+      code = kOrthoLost;
+      break;
+    }
+    code = piv < kPivAgain ? kOrthoAgain : code;
     if (qr == 0 && i >= k && i < r) {
-      const double v = s * s_piv;
-      Gm[(int64_t)i * rmax + k] = i == k ? s_piv : v;
+      const double ip = 1.0 / sqrt(piv), v = s * ip;
+      Gm[(int64_t)i * rmax + k] = i == k ? ip : v;
       if constexpr (LDS)
         lc[col(k) + i] = v;
       else
@@ -676,14 +721,17 @@ __global__ __launch_bounds__(1024) void k_z_chol(double* __restrict__ G, double*
     }
     __syncthreads();
   }
+  if (threadIdx.x == 0) state[mat] = 4 * round + code;
 }
 
-// Z <- L^-1 Z: every component of the vectors on its own, grid (n / 64,
-// matrices), lane = component
-__global__ __launch_bounds__(64) void k_z_solve(double* __restrict__ Z, const double* __restrict__ G, int n, int rk,
-                                                int rv, int rmax) {
+// Z <- L^-1 Z where this round found a factor: every component of the vectors
+// on its own, grid (n / 64, matrices), lane = component
+__global__ __launch_bounds__(64) void k_z_solve(double* __restrict__ Z, const double* __restrict__ G,
+                                                const int32_t* __restrict__ info, const int32_t* __restrict__ state,
+                                                int n, int rk, int rv, int rmax, int round) {
   const int64_t mat = blockIdx.y;
   const int r = (mat & 1) == 0 ? rk : rv;
+  if (info[mat] || (state[mat] >> 2) != round || (state[mat] & 3) == kOrthoLost) return;
   __shared__ double z[256][64];
   const int lane = threadIdx.x;
   double* Zm = Z + mat * rmax * n + blockIdx.x * 64 + lane;
@@ -765,11 +813,12 @@ __global__ __launch_bounds__(256, 1) void k_tri_back(TriState S, double* __restr
 // bases[b][g][d][c] = component d of vector c (largest eigenvalue first) of
 // matrix (b * nb + g) * 2 + side, in the storage format, for the configured
 // rank's columns c < rank_*; the padding columns up to the storage width
-// (stride_*) are zero.  A matrix that is not finite (info != 0) gets quiet-NaN
-// bases, so the failure reaches the caller.
+// (stride_*) are zero.  A matrix that is not finite (info != 0), or whose
+// vectors were lost in every round, gets quiet-NaN bases, so the failure
+// reaches the caller.
 template <typename T>
 __global__ __launch_bounds__(256) void k_write_bases(const double* __restrict__ Z, const int32_t* __restrict__ info,
-                                                     T* __restrict__ bases_k, T* __restrict__ bases_v, int B, int nb,
+                                                     const int32_t* __restrict__ state, T* __restrict__ bases_k, T* __restrict__ bases_v, int B, int nb,
                                                      int Dg, int stride_k, int stride_v, int rank_k, int rank_v,
                                                      int rmax) {
   const int side = blockIdx.y;
@@ -781,7 +830,7 @@ __global__ __launch_bounds__(256) void k_write_bases(const double* __restrict__ 
     const int64_t bg = e / ((int64_t)stride * Dg);
     const int64_t mat = bg * 2 + side;
     const double v = c < rank ? Z[(mat * rmax + c) * Dg + d] : 0.0;
-    store_elem(side ? bases_v : bases_k, e, info[mat] == 0 ? v : __builtin_nan(""));
+    store_elem(side ? bases_v : bases_k, e, info[mat] == 0 && (state[mat] & 3) != kOrthoLost ? v : __builtin_nan(""));
   }
 }
 
@@ -798,7 +847,7 @@ void bases_sample_counts(int64_t T, double eta, int* n_uniform, int* n_recent) {
 
 namespace {
 struct BasesLayout {
-  size_t m, v, y, d, e, tau, lam, norm, info, z, g, lt, inv, part, idx, total;
+  size_t m, v, y, d, e, tau, lam, norm, info, state, z, g, lt, inv, part, idx, total;
 };
 BasesLayout bases_layout(const Problem& P, int n_s) {
   const size_t nmat = (size_t)P.B * 2 * P.nb, Dg = P.Dg, r = std::max(P.rank_cfg, P.rank_v_cfg);
@@ -817,6 +866,7 @@ BasesLayout bases_layout(const Problem& P, int n_s) {
   put(l.lam, nmat * r * 8);
   put(l.norm, nmat * 8);
   put(l.info, nmat * 4);
+  put(l.state, nmat * 4);
   put(l.z, nmat * r * Dg * 8);
   put(l.g, nmat * r * r * 8);
   put(l.lt, nmat * r * r * 8);
@@ -828,21 +878,26 @@ BasesLayout bases_layout(const Problem& P, int n_s) {
 }
 
 template <int NC>
-void launch_eigen(const TriState& S, double* lam, double* norm, int32_t* info, double* Z, double* G, double* LT,
-                  int nmat, int rk, int rv, hipStream_t st) {
+void launch_eigen(const TriState& S, double* lam, double* norm, int32_t* info, int32_t* state, double* Z, double* G,
+                  double* LT, int nmat, int rk, int rv, hipStream_t st) {
   constexpr int n = NC * 256;
   const int rmax = std::max(rk, rv), ev = 2048 / n;
   for (int j = 0; j < n; ++j)
     hipLaunchKernelGGL(k_tridiag_step<NC>, dim3(n / kTriRows, nmat), dim3(256), 0, st, S, j);
   hipLaunchKernelGGL(k_tri_values, dim3((rmax + 3) / 4, nmat), dim3(256), 0, st, S.d, S.e, lam, norm, info, n, rk, rv,
                      rmax);
-  hipLaunchKernelGGL(k_tri_vectors, dim3((rmax + ev - 1) / ev, nmat), dim3(64), 0, st, S.d, S.e, lam, norm, info, Z, n,
-                     rk, rv, rmax, ev);
   const int rt = (rmax + 15) / 16;
-  hipLaunchKernelGGL(k_z_gram, dim3(rt * (rt + 1) / 2, nmat), dim3(256), 0, st, Z, G, n, rk, rv, rmax);
-  hipLaunchKernelGGL(rmax <= kCholLds ? k_z_chol<true> : k_z_chol<false>, dim3(nmat), dim3(1024), 0, st, G, LT, rk, rv,
-                     rmax);
-  hipLaunchKernelGGL(k_z_solve, dim3(n / 64, nmat), dim3(64), 0, st, Z, G, n, rk, rv, rmax);
+  // a matrix whose vectors are orthonormal after a round returns at once from
+  // the later ones (2 us a launch)
+  for (int round = 0; round < kOrthoRounds; ++round) {
+    hipLaunchKernelGGL(k_tri_vectors, dim3((rmax + ev - 1) / ev, nmat), dim3(64), 0, st, S.d, S.e, lam, norm, info,
+                       state, Z, n, rk, rv, rmax, ev, round);
+    hipLaunchKernelGGL(k_z_gram, dim3(rt * (rt + 1) / 2, nmat), dim3(256), 0, st, Z, G, info, state, n, rk, rv, rmax,
+                       round);
+    hipLaunchKernelGGL(rmax <= kCholLds ? k_z_chol<true> : k_z_chol<false>, dim3(nmat), dim3(1024), 0, st, G, LT, info,
+                       state, rk, rv, rmax, round);
+    hipLaunchKernelGGL(k_z_solve, dim3(n / 64, nmat), dim3(64), 0, st, Z, G, info, state, n, rk, rv, rmax, round);
+  }
   hipLaunchKernelGGL(k_tri_back<NC>, dim3((rmax + 3) / 4, nmat), dim3(256), 0, st, S, Z, rk, rv, rmax);
 }
 }  // namespace
@@ -863,6 +918,7 @@ hipError_t launch_prefill_bases(const Problem& P, int64_t n_rows, const void* s_
   auto at = [&](size_t o) { return reinterpret_cast<double*>(w + o); };
   const TriState S{at(l.m), at(l.v), at(l.y), at(l.d), at(l.e), at(l.tau)};
   int32_t* info = reinterpret_cast<int32_t*>(w + l.info);
+  int32_t* state = reinterpret_cast<int32_t*>(w + l.state);
   double *inv = at(l.inv), *part = at(l.part), *Z = at(l.z);
   int32_t* idx = reinterpret_cast<int32_t*>(w + l.idx);
   const int nb = P.nb, Dg = P.Dg, Dp = P.Dp, nmat = P.B * 2 * nb;
@@ -881,7 +937,7 @@ hipError_t launch_prefill_bases(const Problem& P, int64_t n_rows, const void* s_
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int rk = P.rank_cfg, rv = P.rank_v_cfg;
 #define S4R_EIGEN_CASE(NC) \
-  case NC: launch_eigen<NC>(S, at(l.lam), at(l.norm), info, Z, at(l.g), at(l.lt), nmat, rk, rv, st); break;
+  case NC: launch_eigen<NC>(S, at(l.lam), at(l.norm), info, state, Z, at(l.g), at(l.lt), nmat, rk, rv, st); break;
   switch (Dg / 256) {
     S4R_EIGEN_CASE(1)
     S4R_EIGEN_CASE(2)
@@ -897,10 +953,10 @@ hipError_t launch_prefill_bases(const Problem& P, int64_t n_rows, const void* s_
   const int64_t nel = (int64_t)P.B * nb * Dg * std::max(P.rank, P.rank_v);
   const dim3 grid((unsigned)std::min<int64_t>((nel + 255) / 256, 4096), 2);
   if (P.dtype == S4R_BF16)
-    hipLaunchKernelGGL(k_write_bases<uint16_t>, grid, dim3(256), 0, st, Z, info, (uint16_t*)bases_k,
+    hipLaunchKernelGGL(k_write_bases<uint16_t>, grid, dim3(256), 0, st, Z, info, state, (uint16_t*)bases_k,
                        (uint16_t*)bases_v, P.B, nb, Dg, P.rank, P.rank_v, rk, rv, std::max(rk, rv));
   else
-    hipLaunchKernelGGL(k_write_bases<float>, grid, dim3(256), 0, st, Z, info, (float*)bases_k, (float*)bases_v, P.B,
+    hipLaunchKernelGGL(k_write_bases<float>, grid, dim3(256), 0, st, Z, info, state, (float*)bases_k, (float*)bases_v, P.B,
                        nb, Dg, P.rank, P.rank_v, rk, rv, std::max(rk, rv));
   if (idx_out) e = hipMemcpyAsync(idx_out, idx, (size_t)n_s * 4, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipGetLastError();

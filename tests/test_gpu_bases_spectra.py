@@ -72,3 +72,55 @@ def test_bases_of_input_that_is_not_finite():
     torch.cuda.synchronize()
     assert torch.isnan(bk[1]).all()
     assert torch.isfinite(bk[0]).all() and torch.isfinite(bv).all()
+
+
+def _degenerate(kind, n, Dp, k, rng):
+    if kind == "orthogonal":                   # k mutually orthogonal +-1 rows, each repeated: k equal eigenvalues
+        H = np.ones((1, 1))
+        while len(H) < Dp:
+            H = np.block([[H, H], [H, -H]])
+        pick = H[rng.permutation(Dp)[:k]][:, rng.permutation(Dp)] * rng.choice([-1, 1], (1, Dp))
+        return pick[np.arange(n) % k]
+    if kind == "few":                          # k distinct rows: zeros from eigenvalue k + 1 on
+        return rng.standard_normal((k, Dp))[np.arange(n) % k]
+    if kind == "blocks":                       # k copies of one block on the diagonal: multiplicity k
+        b, m = Dp // k, n // k
+        X, src = np.zeros((n, Dp)), rng.standard_normal((m, b))
+        for i in range(k):
+            X[i * m:(i + 1) * m, i * b:(i + 1) * b] = src
+        return X
+    return np.full((n, Dp), 1.5)               # "constant"
+
+
+@pytest.mark.parametrize("kind,hkv,rank,n,k", [
+    ("orthogonal", 2, 16, 288, 16), ("orthogonal", 2, 64, 320, 64), ("orthogonal", 2, 160, 320, 160),
+    ("orthogonal", 2, 256, 512, 256), ("orthogonal", 4, 160, 480, 160), ("orthogonal", 4, 256, 768, 256),
+    ("orthogonal", 8, 128, 384, 128), ("orthogonal", 8, 256, 512, 256), ("orthogonal", 16, 160, 480, 160),
+    ("few", 2, 256, 300, 1), ("few", 4, 64, 300, 2), ("few", 4, 256, 300, 3), ("few", 8, 160, 300, 5),
+    ("few", 8, 256, 300, 3), ("few", 16, 192, 300, 1), ("blocks", 2, 96, 512, 4), ("blocks", 8, 160, 1024, 2),
+    ("blocks", 8, 256, 1024, 8), ("constant", 4, 64, 300, 1), ("constant", 8, 256, 300, 1),
+])
+def test_bases_of_coinciding_eigenvalues(kind, hkv, rank, n, k):
+    """Wanted eigenvalues that are equal: whichever vectors of their space come
+    out, they are orthonormal and hold its energy."""
+    dh, draws = 128, 3
+    Dp = hkv * dh
+    c = s4r.make_config(batch=draws, n_q_heads=hkv, n_kv_heads=hkv, head_dim=dh, rank=rank, capacity=(n + 15) // 16 * 16)
+    rng = np.random.default_rng(n + rank + k)
+    S = [torch.from_numpy(np.stack([_degenerate(kind, n, Dp, k, rng) for _ in range(draws)])).to(torch.bfloat16)
+         for _ in range(2)]
+    got = s4r.prefill_bases(c, n, *[x.cuda() for x in S], eta=1.0)
+    again = s4r.prefill_bases(c, n, *[x.cuda() for x in S], eta=1.0)
+    torch.cuda.synchronize()
+    for x, basis, rep in zip(S, got, again):
+        assert torch.equal(basis, rep)
+        for b in range(draws):
+            X = x[b].to(torch.float64).numpy()
+            X = X / np.linalg.norm(X, axis=1, keepdims=True)
+            w = np.linalg.eigvalsh(X.T @ X)[::-1]
+            Q = basis[b, 0, :, :rank].cpu().to(torch.float64).numpy()
+            # bf16 rounding of the entries, 2^-9 relative each: the bounds of the spectra above
+            off = np.abs(Q.T @ Q - np.eye(rank)).max()
+            assert off <= 1e-2, f"{kind} {Dp} rank {rank}: orthonormal to {off:.1e}"
+            own = ((X @ Q) ** 2).sum(axis=0)
+            assert np.all(np.abs(own - w[:rank]) <= 1e-2 * w[:rank] + 2e-5 * w[0])
