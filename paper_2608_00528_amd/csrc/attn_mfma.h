@@ -515,15 +515,18 @@ namespace s4r {
 
 // tiles per workgroup: the smallest even count whose workgroups fit in one
 // round of the chip (the kernel's workgroups per CU), at most kMaxSplit
-// splits; with an index list, 0 when the list needs more than kTileMax tiles
-// per workgroup (the general kernel then runs)
+// splits.  With an index list a workgroup takes at most kTileMax tiles: past
+// that 0 with equal ranks (the general kernel then runs), kTileMax in more
+// than one round with unequal ones, for which there is no other kernel (0 when
+// kMaxSplit splits do not hold the list either, which the step refuses)
 inline int attn_tiles_per_wg(const Problem& P, int ntile, bool ident) {
   const int slots = 256 * attn_tiles_waves(P.rank / 32, P.rank_v / 32, P.G > 4 ? 2 : 1);
   const int ns_target = std::max(1, slots / std::max(1, P.B * P.hkv));
   int tpw = (ntile + ns_target - 1) / ns_target;
   tpw = std::max(2, (tpw + 1) / 2 * 2);
   while ((ntile + tpw - 1) / tpw > kMaxSplit) tpw += 2;
-  return (ident || tpw <= kTileMax) ? tpw : 0;
+  if (ident || tpw <= kTileMax) return tpw;
+  return P.rank_v != P.rank && ntile <= kMaxSplit * kTileMax ? kTileMax : 0;
 }
 
 template <int RBH, int RBV, int NW, int NMH, bool IDENT>
