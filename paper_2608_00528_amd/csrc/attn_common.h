@@ -23,7 +23,8 @@ __device__ __forceinline__ void rope_cs_fixed(int64_t pos, uint64_t F, float& c,
 // theta^(-2 f / d_h) / (2 pi) = ratio^f / (2 pi) with ratio = theta^(-2 / d_h)
 // (computed once on the host in fp64; ratio 0 disables RoPE).  ratio^f0 by
 // repeated squaring: about 2^-50 relative, so the phase stays exact to about
-// 2^-32 revolutions for any position below 2^18.
+// 2^-32 revolutions for any position below 2^18.  Whole revolutions per position
+// (theta below about 0.16) drop out: the position is an integer.
 __device__ __forceinline__ void rope_freqs_fixed(double ratio, int f0, uint64_t (&F)[4]) {
   double p = 1.0, base = ratio;
   for (int e = f0; e > 0; e >>= 1) {
@@ -32,7 +33,8 @@ __device__ __forceinline__ void rope_freqs_fixed(double ratio, int f0, uint64_t 
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    F[v] = (ratio == 0.0) ? 0ull : (uint64_t)(p * 0.15915494309189535 * 18446744073709551616.0);
+    const double rev = p * 0.15915494309189535;
+    F[v] = (ratio == 0.0) ? 0ull : (uint64_t)((rev - floor(rev)) * 18446744073709551616.0);
     p *= ratio;
   }
 }
