@@ -127,7 +127,8 @@ __global__ __launch_bounds__(256) void k_attn_combine(
   __syncthreads();
   // ---- (max, sum) of the extra tokens, global maximum, split weights (wave 0) ------------
   if (wave == 0) {
-    float mx = -INFINITY;
+    // (finite also where every logit is -inf: such tokens weigh 0 beside others)
+    float mx = -__FLT_MAX__;
     for (int e = lane; e < n_extra; e += 64) mx = fmaxf(mx, lg[e]);
     mx = wave_max(mx);
     float sm = 0.f;

@@ -71,3 +71,32 @@ def test_reconstruction(hq, hkv, dh, rank, nb, m, B, dtype):
         ref = decode.reconstruct(rows, basis.to(torch.float64).numpy())
         # up to 224 products of unit normals in fp32: some 1e-6 of a row's largest value
         assert rel_err_rows(out.cpu().numpy(), ref) < 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("sinks,rows", [(True, False), (False, True), (True, True)])
+def test_logits_of_minus_infinity(dtype, sinks, rows):
+    """Keys whose logits overflow to -inf weigh nothing, whether they are all the
+    sinks or all rows of a split; NaN when no key is left."""
+    hq, hkv, dh, n_sink, m = 4, 2, 64, 3, 40
+    c, idx, q, sk, sv, rng = _draw(hq, hkv, dh, 32, 1, n_sink, m, 100, 1, dtype, 5)
+    c.rope_theta = 0.0                         # no rotation: the first dim alone decides
+    q[..., 0] = 100.0
+    kh, vh = (rng.standard_normal((1, m, hkv * dh)).astype(np.float32) for _ in range(2))
+    lost_s = np.full(n_sink, sinks)
+    lost_r = np.full(m, rows)
+    if not sinks:
+        lost_r[:8] = False                     # one split keeps its rows
+    sk.view(1, n_sink, hkv, dh)[:, lost_s, :, 0] = -3e38
+    kh.reshape(1, m, hkv, dh)[:, lost_r, :, 0] = -3e38
+    out = s4r.sparse_attn(c, 100, q.cuda(), sk.cuda(), sv.cuda(), dev(idx.astype(np.int32), torch.int32),
+                          dev(kh, torch.float32), dev(vh, torch.float32), s4r.alloc_workspace(c)).cpu().numpy()
+    if sinks and rows:
+        assert np.isnan(out).all()
+        return
+    f64 = lambda x: x.to(torch.float64).numpy()  # noqa: E731
+    keys = np.concatenate([f64(sk)[:, ~lost_s], kh[:, ~lost_r]], axis=1)
+    vals = np.concatenate([f64(sv)[:, ~lost_s], vh[:, ~lost_r]], axis=1)
+    ref = decode.attend(f64(q), keys, vals, np.zeros((1, keys.shape[1])), np.zeros(1), 0.0, hkv)
+    # logits up to about 40, whose fp32 rounding of 4e-6 goes through the exponential
+    assert rel_err_rows(out, ref) < 1e-4
