@@ -146,14 +146,17 @@ __global__ __launch_bounds__(kPfWaves * 64, 2) void k_prefill_project(
 #pragma unroll
     for (int n = 0; n < NCB; ++n) acc[i][n] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // issue order per wave: slice 0, rows 0, slice 1, rows 1, then in step st
-  // rows st + 2 and slice st + 2: at the top of a step only the next step's
-  // loads may still be in flight
+  // issue order per wave: slice 0 and rows 0, slice 1 and rows 1, then in step
+  // st rows st + 2 and slice st + 2: at the top of a step only the next step's
+  // loads may still be in flight.  The waits count loads, so no load may move
+  // from one step's group to another's (the scheduling barriers)
   Op8 a0[kPfTiles][2], a1[kPfTiles][2], a2[kPfTiles][2];
   S4R_PF_ISSUE_SLICE(bt0, 0);
   load_rows(0, a0);
+  __builtin_amdgcn_sched_barrier(0);
   S4R_PF_ISSUE_SLICE(bt1, 1);
   load_rows(1, a1);
+  __builtin_amdgcn_sched_barrier(0);
   const int koff = (kq ^ ((slot >> 1) & 3)) * 8;
   auto step = [&](auto buf, auto last, int st, const Op8 (&a)[kPfTiles][2], Op8 (&next)[kPfTiles][2])
                   __attribute__((always_inline)) {
