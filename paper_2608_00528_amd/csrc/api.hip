@@ -408,8 +408,8 @@ s4r_status s4r_prefill_project(const s4r_config* cfg, int64_t n_rows, const void
     return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for equal key and value ranks");
   if (P.rank / 32 < 1 || P.rank / 32 > 6)
     return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for rank 32 .. 192 (rank %d)", P.rank);
-  if ((P.hkv * P.dh / P.nb) % 32)
-    return fail(S4R_ERR_UNSUPPORTED, "basis group width %d is not a multiple of 32", P.hkv * P.dh / P.nb);
+  if (P.Dg % 64)                                     // the kernel's step (always so with head_dim 64 or 128)
+    return fail(S4R_ERR_UNSUPPORTED, "basis group width %d is not a multiple of 64", P.Dg);
   if (n_rows < 1 || n_rows > P.cap)
     return fail(S4R_ERR_BAD_SHAPE, "n_rows = %lld outside [1, capacity = %lld]", (long long)n_rows,
                 (long long)P.cap);
