@@ -27,11 +27,11 @@ CFLAGS = [
     "-fPIC",
     "-Wall",
     "-Wno-unused-function",
-    # no packed fp32 VALU instructions in the generated code
     # the first 16 dwords of every kernel's arguments arrive in registers instead
     # of through a scalar load that every wave of a dependent chain waits for:
     # 0.6 to 1.0 us of a decode step's 37 to 82 us
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
+    # no packed fp32 VALU instructions in the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(HERE, "..", "include"),
 ]

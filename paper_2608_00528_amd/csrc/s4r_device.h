@@ -8,7 +8,6 @@
 
 namespace s4r {
 
-constexpr int kWave = 64;
 constexpr int kTileTok = 16;   // tokens per coefficient tile
 constexpr int kBlkCol = 32;    // latent columns per coefficient block
 
@@ -152,19 +151,6 @@ __device__ __forceinline__ void batched_copy16(int n, SrcOf src_of, DstOf dst_of
     for (int k = 0; k < PER; ++k) r[k] = *src_of(min(base + k * (int)blockDim.x + (int)threadIdx.x, n - 1));
 #pragma unroll
     for (int k = 0; k < PER; ++k) *dst_of(min(base + k * (int)blockDim.x + (int)threadIdx.x, n - 1)) = r[k];
-  }
-}
-
-// same for 4-byte items; src_of(i) returns the value, dst_of(i, v) stores it
-template <int PER, typename SrcOf, typename DstOf>
-__device__ __forceinline__ void batched_copy4(int n, SrcOf src_of, DstOf dst_of) {
-  if (n <= 0) return;
-  for (int base = 0; base < n; base += PER * (int)blockDim.x) {
-    float r[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) r[k] = src_of(min(base + k * (int)blockDim.x + (int)threadIdx.x, n - 1));
-#pragma unroll
-    for (int k = 0; k < PER; ++k) dst_of(min(base + k * (int)blockDim.x + (int)threadIdx.x, n - 1), r[k]);
   }
 }
 
