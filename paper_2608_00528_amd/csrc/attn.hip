@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(
   const int n_extra = s_sink + n_win;
   const int half = dh / 2;
   const int64_t pb = ((int64_t)b * hq + h) * kMaxSplit;
-  const float inv_sqrt_d = 1.0f / sqrtf((float)dh);
+  const float sqrt_d = sqrtf((float)dh);
 
   __shared__ float qr[128];
   __shared__ uint64_t fq[64];
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(
       part = qr[lane] * (kl * c - kh * sn) + qr[lane + half] * (kh * c + kl * sn);
     }
     part = wave_sum(part);
-    if (lane == 0) lg[e] = part * inv_sqrt_d;
+    if (lane == 0) lg[e] = part / sqrt_d;
   }
   __syncthreads();
   // ---- (max, sum) of the extra tokens, global maximum, split weights (wave 0) ------------
