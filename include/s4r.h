@@ -209,7 +209,7 @@ s4r_status s4r_decode_step(const s4r_config* cfg, int64_t L, const void* q,
  * of s4r_decode_step without ws / ws_bytes.  The workspace is a 64 MiB array
  * the library holds on each device that runs this call (from its first call
  * on the device until the process ends); the call itself allocates nothing.
- * A configuration whose s4r_workspace_size exceeds 64 MiB returns
+ * A configuration whose step needs more than 64 MiB of scratch returns
  * S4R_ERR_WORKSPACE before anything is launched.  The stream must belong to
  * the current device.  Every call on a device shares that device's array and
  * leaves its contents behind (the step clears what it needs cleared itself):

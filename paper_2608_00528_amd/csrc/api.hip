@@ -175,6 +175,25 @@ Layout layout(const Problem& P) {
   return l;
 }
 
+// which configurations the bulk projection is built for; its transposed bases
+// lie at the start of the workspace
+s4r_status check_projection(const Problem& P) {
+  if (P.dtype != S4R_BF16) return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for bf16 storage only");
+  if (P.rank_v != P.rank)
+    return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for equal key and value ranks");
+  if (P.rank / 32 < 1 || P.rank / 32 > 6)
+    return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for rank 32 .. 192 (rank %d)", P.rank);
+  if (P.Dg % 64)                                     // the kernel's step (always so with head_dim 64 or 128)
+    return fail(S4R_ERR_UNSUPPORTED, "basis group width %d is not a multiple of 64", P.Dg);
+  return S4R_OK;
+}
+// what the size query reports: the scratch of every other call, and of the
+// projection where it is built
+size_t workspace_bytes(const Problem& P) {
+  const size_t n = layout(P).total;
+  return check_projection(P) == S4R_OK ? std::max(n, align256(prefill_ws_bytes(P))) : n;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 #define S4R_REQ(ptr)                                                                     \
@@ -187,13 +206,16 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
     if ((ptr) && !aligned16(ptr)) return fail(S4R_ERR_MISALIGNED, "%s is not 16-byte aligned", #ptr); \
   } while (0)
 
-s4r_status check_ws(const Problem& P, void* ws, size_t ws_bytes) {
+s4r_status check_ws(void* ws, size_t ws_bytes, size_t need) {
   if (!ws) return fail(S4R_ERR_NULL_ARG, "ws is NULL");
   if (((uintptr_t)ws & 255) != 0) return fail(S4R_ERR_MISALIGNED, "ws is not 256-byte aligned");
-  const size_t need = layout(P).total;
   if (ws_bytes < need)
     return fail(S4R_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, need);
   return S4R_OK;
+}
+
+s4r_status check_ws(const Problem& P, void* ws, size_t ws_bytes) {
+  return check_ws(ws, ws_bytes, layout(P).total);
 }
 
 s4r_status check_L(const Problem& P, int64_t L) {
@@ -299,7 +321,7 @@ s4r_status s4r_workspace_size(const s4r_config* cfg, size_t* bytes) {
   s4r_status st = make_problem(cfg, P);
   if (st) return st;
   if (!bytes) return fail(S4R_ERR_NULL_ARG, "bytes is NULL");
-  *bytes = layout(P).total;
+  *bytes = workspace_bytes(P);
   return ok();
 }
 
@@ -403,13 +425,7 @@ s4r_status s4r_prefill_project(const s4r_config* cfg, int64_t n_rows, const void
   Problem P;
   s4r_status st = make_problem(cfg, P);
   if (st) return st;
-  if (P.dtype != S4R_BF16) return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for bf16 storage only");
-  if (P.rank_v != P.rank)
-    return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for equal key and value ranks");
-  if (P.rank / 32 < 1 || P.rank / 32 > 6)
-    return fail(S4R_ERR_UNSUPPORTED, "the bulk projection is built for rank 32 .. 192 (rank %d)", P.rank);
-  if (P.Dg % 64)                                     // the kernel's step (always so with head_dim 64 or 128)
-    return fail(S4R_ERR_UNSUPPORTED, "basis group width %d is not a multiple of 64", P.Dg);
+  if ((st = check_projection(P))) return st;
   if (n_rows < 1 || n_rows > P.cap)
     return fail(S4R_ERR_BAD_SHAPE, "n_rows = %lld outside [1, capacity = %lld]", (long long)n_rows,
                 (long long)P.cap);
@@ -419,8 +435,7 @@ s4r_status s4r_prefill_project(const s4r_config* cfg, int64_t n_rows, const void
   S4R_REQ(bases_v);
   S4R_REQ(coef_k);
   S4R_REQ(coef_v);
-  if ((st = check_ws(P, ws, ws_bytes))) return st;     // the transposed bases use its first bytes
-  if (prefill_ws_bytes(P) > layout(P).total) return fail(S4R_ERR_WORKSPACE, "workspace too small for the bases");
+  if ((st = check_ws(ws, ws_bytes, workspace_bytes(P)))) return st;   // the transposed bases use its first bytes
   return hip_status(launch_prefill_project(P, n_rows, s_k, s_v, bases_k, bases_v, coef_k, coef_v, ws, stream),
                     "s4r_prefill_project launch");
 }

@@ -38,3 +38,26 @@ def test_projection_edges(hkv, dh, nb, rank, n, B):
         assert np.all(np.abs(g[:, :n, :, :rank] - ref) <= bound)
         assert np.all(g[:, :n, :, rank:] == 0)                   # padding columns of a rank off 32
         assert np.all(g[:, n:] == 3.0)                           # rows past the prompt untouched
+
+
+@pytest.mark.parametrize("hkv,dh,rank,n,B", [(8, 128, 192, 5, 2), (16, 64, 160, 16, 4), (4, 64, 96, 30, 1)])
+def test_projection_in_the_queried_workspace(hkv, dh, rank, n, B):
+    """A capacity so small that the transposed bases are the larger part of the
+    workspace: what the size query says is enough, and its last byte is not passed."""
+    rng = np.random.default_rng(n + rank)
+    Dp, cap = hkv * dh, (n + 15) // 16 * 16
+    c = s4r.make_config(batch=B, n_q_heads=hkv, n_kv_heads=hkv, head_dim=dh, rank=rank, capacity=cap)
+    size = s4r.workspace_size(c)
+    assert size >= 2 * B * Dp * rank * 2
+    guarded = torch.full((size + 4096,), 7, dtype=torch.uint8, device="cuda")
+    rows = [torch.from_numpy(rng.standard_normal((B, n, Dp))).to(torch.bfloat16) for _ in range(2)]
+    bases = [torch.from_numpy(rng.standard_normal((B, 1, Dp, rank))).to(torch.bfloat16) for _ in range(2)]
+    coef = [torch.zeros((B, cap, rank), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    s4r.prefill_project(c, n, *[x.cuda() for x in rows], *[x.cuda() for x in bases], *coef, guarded[:size])
+    torch.cuda.synchronize()
+    assert torch.all(guarded[size:] == 7)
+    for x, basis, got in zip(rows, bases, coef):
+        a, w = x.to(torch.float64).numpy(), basis[:, 0].to(torch.float64).numpy()
+        g = s4r.unpack_coef(c, n, got).cpu().to(torch.float64).numpy()
+        bound = 2.0 ** -8 * np.abs(a @ w) + Dp * 2.0 ** -24 * (np.abs(a) @ np.abs(w))
+        assert np.all(np.abs(g - a @ w) <= bound)
