@@ -158,8 +158,8 @@ Layout layout(const Problem& P) {
   sizes[kIdx] = B * P.m_max * 4;
   sizes[kPartMl] = B * P.hq * kMaxSplit * 2 * 4;
   sizes[kPartO] = B * P.hq * kMaxSplit * P.dh * 4;
-  // no kernel uses it; it keeps the workspace at the size that callers have
-  // allocated and that the entry points' size checks compare with
+  // no kernel uses it, nor the second half of kCand: the size decides which
+  // configurations the step without a workspace refuses, and those stay refused
   sizes[kReserved] = B * P.hq * (P.s + P.m_max) * 4;
   sizes[kCandCount] = B * sel_groups_max(P) * 4;
   sizes[kAboveCount] = B * sel_groups_max(P) * 4;
