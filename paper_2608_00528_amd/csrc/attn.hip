@@ -198,37 +198,46 @@ static void launch_combine_t(const Problem& P, const Workspace& ws, int64_t L, i
 // ---------------------------------------------------------------------------
 // explicit reconstruction: K^[b, n, :] = C^K[b, idx[b, n]] (B^K)^T (fp32 out)
 // ---------------------------------------------------------------------------
-// grid (ceil(m / 16), h_kv, B), four waves: wave w forms the key (w < 2) or
-// value rows of 16 tokens over half w % 2 of head j's dims.  Bound by latency
-// at decode sizes (m = 1088, 8 heads: 9 MB written), so every basis block of a
-// dims step is requested before the first product, and the basis is the A
-// operand: a lane then holds four consecutive dims of one token and stores 16
-// bytes.  15.3 -> 11.8 us at m = 1088, rank 160 (one wave per 16 tokens walking
-// both sides and all dims before).
-template <typename T, int RBH>
+// grid (ceil(m / (16 NT)), h_kv, B), four waves: wave w forms the key (w < 2)
+// or value rows of NT tiles of 16 tokens over half w % 2 of head j's dims.
+// Bound by latency at decode sizes (m = 1088, 8 heads: 9 MB written), so every
+// basis block of a dims step is requested before the first product, and the
+// basis is the A operand: a lane then holds four consecutive dims of one token
+// and stores 16 bytes.  A tile's share of the basis is five times what it
+// writes at rank 160, so larger m is bound by reading it from L2: one read
+// serves all NT tiles.  Whole call at rank 160, 8 heads, one wave per 16 tokens
+// walking both sides / NT 1 / NT 4: 11.1 / 8.9 / 8.0 us at m = 1088, 31.1 / 34.5 /
+// 24.6 at 8000, 86.8 / 96.1 / 65.3 at 24000; fp32 (NT 2) 35.0 / 20.4 / 17.5 and
+// 256 / 274 / 175.
+template <typename T, int RBH, int NT>
 __global__ __launch_bounds__(256) void k_reconstruct(
     const int32_t* __restrict__ idx_all, const T* __restrict__ bases_k, const T* __restrict__ bases_v,
     const T* __restrict__ coef_k, const T* __restrict__ coef_v, float* __restrict__ k_hat,
     float* __restrict__ v_hat, int m, int hkv, int dh, int nb, int rank, int R, int64_t L, int64_t cap,
     int bases_shared) {
   constexpr int NP = Parts<T>::n;
-  const int tile = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+  const int j = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, slot = lane & 15, kg = lane >> 4;
   const int which = w >> 1, half = w & 1;
   const int Dp = hkv * dh, Dg = Dp / nb;
   const int grp = j / (hkv / nb), row0 = (j % (hkv / nb)) * dh, kb0 = grp * rank / 32;
-  const int n = tile * 16 + slot;
-  int64_t tok = (n < m) ? (int64_t)idx_all[(int64_t)b * m + n] : 0;
-  const bool bad = tok < 0 || tok >= L;            // NaN row instead of a read out of range
-  if (bad) tok = 0;
-  const int64_t co = (tok >> 4) * 16 * (int64_t)R + (tok & 15) * 32 + kg * 8;
   const int64_t boff = (bases_shared ? 0 : (int64_t)b * Dp * rank) + (int64_t)grp * Dg * rank;
   const T* cb = (which == 0 ? coef_k : coef_v) + (int64_t)b * cap * R;
   const T* bb = (which == 0 ? bases_k : bases_v) + boff;
-  float* dst = (which == 0 ? k_hat : v_hat) + ((int64_t)b * m + n) * Dp + (int64_t)j * dh;
-  Op8 c[RBH][NP];
+  const int n0 = blockIdx.x * NT * 16 + slot;      // row of this lane in the first tile
+  float* dst = (which == 0 ? k_hat : v_hat) + ((int64_t)b * m + n0) * Dp + (int64_t)j * dh;
+  bool bad[NT];
+  Op8 c[NT][RBH][NP];
 #pragma unroll
-  for (int kb = 0; kb < RBH; ++kb) Parts<T>::load(cb + co + (int64_t)(kb0 + kb) * 512, c[kb]);
+  for (int q = 0; q < NT; ++q) {
+    const int n = n0 + q * 16;
+    int64_t tok = (n < m) ? (int64_t)idx_all[(int64_t)b * m + n] : 0;
+    bad[q] = tok < 0 || tok >= L;                  // NaN row instead of a read out of range
+    if (bad[q]) tok = 0;
+    const int64_t co = (tok >> 4) * 16 * (int64_t)R + (tok & 15) * 32 + kg * 8;
+#pragma unroll
+    for (int kb = 0; kb < RBH; ++kb) Parts<T>::load(cb + co + (int64_t)(kb0 + kb) * 512, c[q][kb]);
+  }
   const int nblk = dh / 32;                        // 16-dim blocks of this wave's half
   constexpr int BST = NP == 1 ? 2 : 1;             // blocks per step (nblk is 2 or 4)
   for (int i0 = 0; i0 < nblk; i0 += BST) {
@@ -240,14 +249,17 @@ __global__ __launch_bounds__(256) void k_reconstruct(
         Parts<T>::load(bb + (int64_t)(row0 + (half * nblk + i0 + u) * 16 + slot) * rank + kb * 32 + kg * 8, bo[u][kb]);
     if constexpr (NP == 1) __builtin_amdgcn_sched_barrier(0);   // the loads stay together, ahead of the products
 #pragma unroll
-    for (int u = 0; u < BST; ++u) {
-      floatx4 d = {0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < NT; ++q)
 #pragma unroll
-      for (int kb = 0; kb < RBH; ++kb) d = mfma_parts<NP, NP>(bo[u][kb], c[kb], d);
-      if (bad) d = floatx4{NAN, NAN, NAN, NAN};
-      // lane holds token slot, dims 4 kg + v of the block
-      if (n < m) *reinterpret_cast<floatx4*>(dst + (half * nblk + i0 + u) * 16 + kg * 4) = d;
-    }
+      for (int u = 0; u < BST; ++u) {
+        floatx4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < RBH; ++kb) d = mfma_parts<NP, NP>(bo[u][kb], c[q][kb], d);
+        if (bad[q]) d = floatx4{NAN, NAN, NAN, NAN};
+        // lane holds token slot, dims 4 kg + v of the block
+        if (n0 + q * 16 < m)
+          *reinterpret_cast<floatx4*>(dst + (int64_t)q * 16 * Dp + (half * nblk + i0 + u) * 16 + kg * 4) = d;
+      }
   }
 }
 
@@ -543,7 +555,16 @@ hipError_t launch_combine_only(const Problem& P, const Workspace& ws, int64_t L,
 template <typename T, int RBH>
 static void launch_rec_t(const Problem& P, int64_t L, int m, const int32_t* idx, const void* bk, const void* bv,
                          const void* ck, const void* cv, float* kh, float* vh, hipStream_t st) {
-  hipLaunchKernelGGL((k_reconstruct<T, RBH>), dim3((m + 15) / 16, P.hkv, P.B), dim3(256), 0, st, idx, (const T*)bk,
+  // tiles per workgroup: as many as the registers hold (four; two of fp32 rows
+  // wider than 96, three operands each), while the workgroups still cover half
+  // the CUs (fp32, bound by its products: four tiles only with one per CU)
+  constexpr bool one = Parts<T>::n == 1;
+  int nt = one || RBH <= 3 ? 4 : 2;
+  while (nt > 1 && (int64_t)((m + 16 * nt - 1) / (16 * nt)) * P.hkv * P.B < (one ? 128 : 64 * nt)) nt >>= 1;
+  auto kern = nt == 1 ? k_reconstruct<T, RBH, 1> : k_reconstruct<T, RBH, 2>;
+  if constexpr (one || RBH <= 3)
+    if (nt == 4) kern = k_reconstruct<T, RBH, 4>;
+  hipLaunchKernelGGL(kern, dim3((m + 16 * nt - 1) / (16 * nt), P.hkv, P.B), dim3(256), 0, st, idx, (const T*)bk,
                      (const T*)bv, (const T*)ck, (const T*)cv, kh, vh, m, P.hkv, P.dh, P.nb, P.rank, P.R, L, P.cap,
                      P.bases_shared);
 }

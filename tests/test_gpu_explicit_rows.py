@@ -100,3 +100,31 @@ def test_logits_of_minus_infinity(dtype, sinks, rows):
     ref = decode.attend(f64(q), keys, vals, np.zeros((1, keys.shape[1])), np.zeros(1), 0.0, hkv)
     # logits up to about 40, whose fp32 rounding of 4e-6 goes through the exponential
     assert rel_err_rows(out, ref) < 1e-4
+
+
+@pytest.mark.parametrize("hkv,dh,rank,m,B,dtype", [
+    # four, two and one tile of 16 rows per workgroup, rows left over in each
+    (8, 128, 160, 1025, 1, "bf16"), (8, 128, 32, 1023, 1, "bf16"), (4, 64, 224, 1000, 1, "bf16"),
+    (16, 64, 96, 530, 2, "bf16"), (8, 128, 96, 2049, 1, "fp32"), (8, 128, 128, 515, 1, "fp32"),
+    (8, 64, 192, 257, 3, "fp32"), (4, 128, 256, 700, 2, "fp32"), (2, 64, 64, 65, 1, "fp32"),
+])
+def test_reconstruction_tiles_per_workgroup(hkv, dh, rank, m, B, dtype):
+    L = 2 * m + 40
+    c, idx, _, _, _, rng = _draw(hkv, hkv, dh, rank, 1, 0, m, L, B, dtype, m)
+    dt, Dp = s4r.storage_dtype(c), hkv * dh
+    rnd = lambda *s: torch.from_numpy(rng.standard_normal(s)).to(dt)  # noqa: E731
+    bases, coefs = [rnd(B, 1, Dp, rank) for _ in range(2)], [rnd(B, c.capacity, rank) for _ in range(2)]
+    idx[:, 7] = [-1, L, L + 5][:B]                               # out of range: a NaN row, nothing else
+    guard = [torch.full((B * m * Dp + 512,), 3.0, device="cuda") for _ in range(2)]
+    s4r.reconstruct(c, L, dev(idx.astype(np.int32), torch.int32), *[x.cuda() for x in bases],
+                    *[s4r.pack_coef(c, c.capacity, x.cuda()) for x in coefs],
+                    *[x[:B * m * Dp].view(B, m, Dp) for x in guard])
+    torch.cuda.synchronize()
+    keep = np.arange(m) != 7
+    for out, basis, coef in zip(guard, bases, coefs):
+        assert torch.all(out[B * m * Dp:] == 3.0)
+        got = out[:B * m * Dp].view(B, m, Dp).cpu().numpy()
+        assert np.isnan(got[:, 7]).all()
+        rows = np.stack([coef[b].to(torch.float64).numpy()[idx[b][keep]] for b in range(B)])
+        # up to 256 products of unit normals in fp32: some 1e-6 of a row's largest value
+        assert rel_err_rows(got[:, keep], decode.reconstruct(rows, basis.to(torch.float64).numpy())) < 1e-5
