@@ -162,8 +162,21 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
   __shared__ int32_t sidx[kTileMax * 16];
   __shared__ float xl[2][2][NW][NMH][4][16];             // partial logits [pair & 1][tile of pair][wave][mh][head][slot]
   // the split's P C^V as bf16 parts: row 4 head + part, columns padded by 16
-  // bytes (the operand reads of 16 rows hit distinct banks)
-  __shared__ __align__(16) uint16_t olat[NMH][16][RBV * 32 + 8];
+  // bytes (the operand reads of 16 rows hit distinct banks).  Beside the other
+  // arrays where the workgroups per CU still fit the 160 KB, else (rank 224 with
+  // more than four heads: one workgroup a CU less, 70.0 against 63.0 us for the
+  // step at 4 x 40k) in the value buffers once they have been read for the last time
+  constexpr int OLS = RBV * 32 + 8;
+  constexpr int kLds = 4 * (RBH + RBV) * 1024 + (int)sizeof(sidx) + (int)sizeof(xl);
+  constexpr bool OL_OWN = (kLds + NMH * 16 * OLS * 2) * attn_tiles_waves(RBH, RBV, NMH) <= 160 * 1024;
+  static_assert(NMH <= 2 && 16 * OLS <= 2 * RBV * 512, "one row group of P C^V per value buffer");
+  __shared__ __align__(16) uint16_t olat_own[OL_OWN ? NMH : 1][OL_OWN ? 16 * OLS : 8];
+  auto olat = [&](int mh) __attribute__((always_inline)) -> uint16_t* {
+    if constexpr (OL_OWN)
+      return &olat_own[mh][0];
+    else
+      return mh == 0 ? &gvA[0][0][0] : &gvB[0][0][0];
+  };
 
   // ---- 1. index list, bases and query requested; then the first two pairs' gathers ---------
   int32_t xi[kTileMax * 16 / (NW * 64)];
@@ -441,6 +454,9 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
     iterate(p, std::integral_constant<int, 0>(), vtc, tokc);
     ++p;
   }
+  // no gather left in flight into the value buffers (a second pair that is never
+  // used when there is one pair only)
+  if constexpr (!OL_OWN) wait_vmcnt<0>();
   // the value basis as B operands (column = dim), overlapping the last pair's softmax
   Op8 bv[2][RBV];
 #pragma unroll
@@ -451,7 +467,7 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
       bv[m][kb].u =
           *reinterpret_cast<const uint4*>(bases_v + boffv + (int64_t)(row0 + d) * rank_v + kb * 32 + kg * 8);
   }
-  lds_barrier();                                   // xl of the last pair complete
+  lds_barrier();                                   // xl of the last pair complete, its rows read
   finish_pair(p, vtc, tokc);
 
   // ---- B^V applied to the split's P C^V: its fp32 values as three bf16 parts in
@@ -468,10 +484,10 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
         const float r1 = x - bf16_bits_to_f32(hi);
         const uint32_t mid = f32_to_bf16_bits(r1);
         const float r2 = r1 - bf16_bits_to_f32(mid);
-        uint16_t* o = &olat[mh][4 * kg][cb * 16 + slot];
+        uint16_t* o = olat(mh) + 4 * kg * OLS + cb * 16 + slot;
         o[0] = (uint16_t)hi;
-        o[RBV * 32 + 8] = (uint16_t)mid;
-        o[2 * (RBV * 32 + 8)] = (uint16_t)f32_to_bf16_bits(r2);
+        o[OLS] = (uint16_t)mid;
+        o[2 * OLS] = (uint16_t)f32_to_bf16_bits(r2);
       }
     }
   lds_barrier();
@@ -482,13 +498,12 @@ __global__ __launch_bounds__(NW * 64, (attn_tiles_waves_per_simd<RBH, RBV, NMH>(
 #pragma unroll
     for (int kb = 0; kb < RBV; ++kb) {
       Op8 a;
-      a.u = *reinterpret_cast<const uint4*>(&olat[mh][slot][kb * 32 + kg * 8]);
+      a.u = *reinterpret_cast<const uint4*>(olat(mh) + slot * OLS + kb * 32 + kg * 8);
 #pragma unroll
       for (int m = 0; m < 2; ++m) od[mh][m] = mfma16x16x32(a, bv[m][kb], od[mh][m]);
     }
   }
-  wait_vmcnt<0>();                                 // no gather left in flight (a second pair that
-                                                   // was never used when there is one pair only)
+  wait_vmcnt<0>();                                 // no gather left in flight
 
   // ---- partial results of the split --------------------------------------------------
 #pragma unroll
