@@ -56,7 +56,14 @@ constexpr int rel_stat_max() {
 // chunks; 512 costs 2.7 and 1 us there).  The histogram copies keep the
 // flush atomics of more workgroups from serialising.
 constexpr int kRelMinWg = 1024;
+// Windows wider than kPoolShared read single values and always take one output
+// per thread, so that a wave reads consecutive words: with TPT consecutive
+// outputs a thread the reads of neighbouring lanes are TPT words apart and
+// conflict (the step over 8 x 128k, 7 columns, with four outputs a thread and one:
+// 141 -> 113 us at a window of 33, 191 -> 131 us at 65).
+constexpr int kPoolShared = 9;
 int relevance_chunk(const Problem& P, int64_t L) {
+  if (P.kappa > kPoolShared) return kRelThreads;
   int c = P.G <= 8 ? 1024 : 512;
   while (c > 256 && (int64_t)P.B * ((L + c - 1) / c) < kRelMinWg) c >>= 1;
   return c;
@@ -67,21 +74,12 @@ int relevance_chunk(const Problem& P, int64_t L) {
 __host__ __device__ constexpr int rel_row(int span) { return (span + 7) / 4 * 4; }
 
 // Pooling (kappa = 2H + 1, stride 1, same length) and aggregation over the G
-// groups for TPT outputs of thread t.  Up to kPoolShared wide they are t TPT ..
-// t TPT + TPT - 1: the windows of neighbouring outputs overlap, so a thread
-// reads TPT + 2H values per group in aligned vectors and shares the maximum of
-// the common part.  H < 0 is the generic path for wider windows, whose single
-// reads of neighbouring lanes would then be TPT words apart and conflict: its
-// outputs are t, t + 256, .., so a wave reads consecutive words (the step over
-// 8 x 128k, 7 columns, TPT 4: 141.6 -> 116.2 us at 33 wide, 192.2 -> 144.7 at 65).
-constexpr int kPoolShared = 9;
-// position of output j of thread t in the chunk
-template <int TPT>
-__device__ __forceinline__ int pool_output(int t, int j, int kappa) {
-  return kappa > kPoolShared ? t + j * kRelThreads : t * TPT + j;
-}
+// groups for outputs o0 .. o0 + TPT - 1 (o0 a multiple of TPT): the windows of
+// neighbouring outputs overlap, so a thread reads TPT + 2H values per group in
+// aligned vectors and shares the maximum of the common part.  H < 0 is the
+// generic path for wider windows (TPT = 1).
 template <int H, int TPT>
-__device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int row, int t, int G, int kappa,
+__device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int row, int o0, int G, int kappa,
                                                int pool_mode, int agg, float (&af)[TPT]) {
   double acc[TPT];
 #pragma unroll
@@ -91,7 +89,7 @@ __device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int
     constexpr int NV = (TPT + 2 * H + TPT - 1) / TPT * TPT;
 #pragma unroll 4
     for (int g = 0; g < G; ++g) {
-      const float* p = vs + g * row + t * TPT;
+      const float* p = vs + g * row + o0;
       float w[NV];
 #pragma unroll
       for (int i = 0; i < NV; i += TPT) {
@@ -138,34 +136,34 @@ __device__ __forceinline__ void pool_aggregate(const float* __restrict__ vs, int
       for (int j = 0; j < TPT; ++j) acc[j] = mean ? acc[j] + (double)a[j] : fmax(acc[j], (double)a[j]);
     }
   } else {
-#pragma unroll
-    for (int j = 0; j < TPT; ++j)
-      for (int g = 0; g < G; ++g) {
-        const float* v = vs + g * row + pool_output<TPT>(t, j, kappa);
-        float a = v[0];
-        double sa = (double)v[0];
-        for (int d = 1; d < kappa; ++d) {
-          a = fmaxf(a, v[d]);
-          sa += (double)v[d];
-        }
-        if (pool_mode != S4R_POOL_MAX) a = (float)(sa / kappa);
-        acc[j] = mean ? acc[j] + (double)a : fmax(acc[j], (double)a);
+    static_assert(TPT == 1, "one output per thread");
+    for (int g = 0; g < G; ++g) {
+      const float* v = vs + g * row + o0;
+      float a = v[0];
+      double sa = (double)v[0];
+      for (int d = 1; d < kappa; ++d) {
+        a = fmaxf(a, v[d]);
+        sa += (double)v[d];
       }
+      if (pool_mode != S4R_POOL_MAX) a = (float)(sa / kappa);
+      acc[0] = mean ? acc[0] + (double)a : fmax(acc[0], (double)a);
+    }
   }
 #pragma unroll
   for (int j = 0; j < TPT; ++j) af[j] = (float)(mean ? acc[j] / G : acc[j]);
 }
 
 template <int TPT>
-__device__ __forceinline__ void pool_dispatch(const float* vs, int row, int t, int G, int kappa, int pool_mode, int agg,
+__device__ __forceinline__ void pool_dispatch(const float* vs, int row, int o0, int G, int kappa, int pool_mode, int agg,
                                               float (&af)[TPT]) {
   switch (kappa / 2) {
-    case 0: pool_aggregate<0, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
-    case 1: pool_aggregate<1, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
-    case 2: pool_aggregate<2, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
-    case 3: pool_aggregate<3, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
-    case 4: pool_aggregate<4, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
-    default: pool_aggregate<-1, TPT>(vs, row, t, G, kappa, pool_mode, agg, af); break;
+    case 0: pool_aggregate<0, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 1: pool_aggregate<1, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 2: pool_aggregate<2, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case 3: pool_aggregate<3, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    case kPoolShared / 2: pool_aggregate<kPoolShared / 2, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af); break;
+    default:                                               // wider: the launch takes TPT = 1
+      if constexpr (TPT == 1) pool_aggregate<-1, TPT>(vs, row, o0, G, kappa, pool_mode, agg, af);
   }
 }
 
@@ -449,20 +447,19 @@ __global__ __launch_bounds__(kRelThreads) void k_relevance(
   }
   // ---- pooling (kappa, stride 1, same length) and aggregation over G -------------------
   float af[TPT];
-  pool_dispatch<TPT>(vs, row, t, G, kappa, pool_mode, agg, af);
+  pool_dispatch<TPT>(vs, row, t * TPT, G, kappa, pool_mode, agg, af);
   const int xo = t0 + t * TPT;
-  const bool whole = TPT > 1 && kappa <= kPoolShared && xo + TPT <= L;   // TPT consecutive outputs in range
-  float* ap = atilde + (int64_t)b * cap;                   // cap is a multiple of 16: xo is aligned for TPT values
+  float* ap = atilde + (int64_t)b * cap + xo;              // cap is a multiple of 16: aligned for TPT values
   if constexpr (TPT == 4) {
-    if (whole) *reinterpret_cast<float4*>(ap + xo) = make_float4(af[0], af[1], af[2], af[3]);
+    if (xo + 3 < L) *reinterpret_cast<float4*>(ap) = make_float4(af[0], af[1], af[2], af[3]);
   } else if constexpr (TPT == 2) {
-    if (whole) *reinterpret_cast<float2*>(ap + xo) = make_float2(af[0], af[1]);
+    if (xo + 1 < L) *reinterpret_cast<float2*>(ap) = make_float2(af[0], af[1]);
   }
 #pragma unroll
   for (int j = 0; j < TPT; ++j) {
-    const int x = t0 + pool_output<TPT>(t, j, kappa);
+    const int x = xo + j;
     if (x < L) {
-      if (!whole) ap[x] = af[j];
+      if (TPT == 1 || xo + TPT > L) ap[j] = af[j];
       if (scores_out) scores_out[(int64_t)b * score_stride + x] = af[j];
     }
     if (x < n_hist) atomicAdd(&hl[selection_key_shift(af[j], key_shift) >> kHistShift], 1u);
